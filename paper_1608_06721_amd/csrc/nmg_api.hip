@@ -1112,6 +1112,8 @@ Phys make_phys(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params)
     P.g = params->g;
     P.alpha = params->alpha;
     P.eps = params->fd_eps;
+    P.eps_rh = 1.0 / P.eps;
+    P.eps_rl = std::fma(-P.eps_rh, P.eps, 1.0) / P.eps;
     P.h_eps = params->h_eps;
     P.eps_r = params->eps_r;
     P.tau = params->tau;
@@ -1878,10 +1880,10 @@ int nmg_batch_newton_mg_solve(nmg_batch *b, const double *const *z, double *cons
         const int order[4] = {0, 1, 1, 0};
         for (int s = 0; s < p.blu_sweeps; ++s)
             for (int q = 0; q < 4; ++q)
-                BHIPCHK(b, launch_b_blu_half(dim, b->d_inst, b->w_plane[0][ti256], b->d_active,
+                BHIPCHK(b, launch_b_blu_half(dim, p.flux, b->d_inst, b->w_plane[0][ti256], b->d_active,
                                              order[q], b->stream));
         BHIPCHK(b, launch_b_isolated(dim, b->d_inst, b->w_cells0, b->d_active, b->stream));
-        BHIPCHK(b, launch_b_assemble(dim, b->f32, b->d_inst, b->w_cells0, b->d_active,
+        BHIPCHK(b, launch_b_assemble(dim, p.flux, b->f32, b->d_inst, b->w_cells0, b->d_active,
                                      b->d_partial, b->stream));
         if ((rc = bctx(b, build_coarse(t)))) return rc;
         if ((rc = batch_norms(b, b->d_active))) return rc;
@@ -1933,7 +1935,7 @@ int nmg_batch_newton_mg_solve(nmg_batch *b, const double *const *z, double *cons
             b->h_mask[k] = b->h_active[k];
         }
         if ((rc = upload_mask(b, b->d_mask, b->h_mask))) return rc;
-        BHIPCHK(b, launch_b_residual(dim, b->d_inst, b->w_cells0, b->d_mask, b->d_partial, b->stream));
+        BHIPCHK(b, launch_b_residual(dim, p.flux, b->d_inst, b->w_cells0, b->d_mask, b->d_partial, b->stream));
         if ((rc = batch_norms(b, b->d_mask))) return rc;
         for (int k = 0; k < n; ++k)
             if (b->h_mask[k]) res[k] = b->h_norm[k];

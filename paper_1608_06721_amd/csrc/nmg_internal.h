@@ -20,6 +20,7 @@ struct Phys {
     int flux, dry_pin;
     double g, alpha, eps, h_eps, eps_r, tau, pos_theta;
     double elen[4];         // |e| of W, E, S, N faces
+    double eps_rh, eps_rl;  // 1/eps as a sum: eps_rh = RN(1/eps), eps_rl the rest (fd_quotient)
     SideDev bc[4];
 };
 
@@ -298,18 +299,18 @@ constexpr int kTileChoices[kNumTiles] = {64, 128, 256, 512};
 // whose active flag is 0.
 hipError_t launch_b_isolated(int dim, const BatchInst *bi, WorkRange w, const int *active,
                              hipStream_t s);
-hipError_t launch_b_assemble(int dim, bool f32, const BatchInst *bi, WorkRange w,
+hipError_t launch_b_assemble(int dim, int flux, bool f32, const BatchInst *bi, WorkRange w,
                              const int *active, double *partial, hipStream_t s);
-hipError_t launch_b_residual(int dim, const BatchInst *bi, WorkRange w, const int *active,
-                             double *partial, hipStream_t s);
+hipError_t launch_b_residual(int dim, int flux, const BatchInst *bi, WorkRange w,
+                             const int *active, double *partial, hipStream_t s);
 hipError_t launch_b_count_iso(const BatchInst *bi, WorkRange w, const int *active,
                               double *partial, hipStream_t s);
 // Per-instance sums of the partials: out[k] = sum of partial[off[k] .. off[k] + cnt[k])
 // in the order of launch_reduce.
 hipError_t launch_b_reduce(const double *partial, const int *off, const int *cnt, int n,
                            const int *active, double *out, hipStream_t s);
-hipError_t launch_b_blu_half(int dim, const BatchInst *bi, WorkRange w, const int *active,
-                             int color, hipStream_t s);
+hipError_t launch_b_blu_half(int dim, int flux, const BatchInst *bi, WorkRange w,
+                             const int *active, int color, hipStream_t s);
 // Fused half-sweep pair of launch_sgs_pair over a work list of 32x16 tiles
 // (2D): flip 0 reads the second colour from x and writes it to xt, flip 1
 // the reverse.

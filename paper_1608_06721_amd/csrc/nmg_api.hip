@@ -124,6 +124,8 @@ struct nmg_batch {
     LevelDev *d_clv = nullptr;            // [n * kMaxLevels] coarse-kernel level tables
     WorkItem *d_work = nullptr;
     WorkRange w_cells0{nullptr, 0};       // 256-cell tiles of level 0
+    WorkRange w_blu{nullptr, 0};          // 256-slot tiles of level 0 in BLU-SGS order
+    bool blu_patch = false;               // that order: patches or rows
     WorkRange w_plane[kMaxLevels][kNumTiles];   // colour-plane tiles per tile length
     WorkRange w_ccells[kMaxLevels];       // 256-cell tiles of level l (Galerkin into l)
     WorkRange w_rchild[kMaxLevels];       // tiles of 256 children of level l's cells (restriction into l)
@@ -936,7 +938,10 @@ int alloc_step1(nmg_ctx *c)
     // level 1 is the largest coarse level; a half sweep launches at most 16
     // lanes per cell of one colour
     const size_t c1 = cells(c->L[1].G);
-    const size_t nparts = (size_t)nblocks(16 * (long)c1);
+    size_t nparts = (size_t)nblocks(16 * (long)c1);
+    for (int l = 1; l <= NL; ++l)
+        for (int lanes : {1, 4, 16})
+            nparts = std::max(nparts, (size_t)blu_half_blocks(level_phys(c, l), lanes));
     size_t tot = nc * c1 + nparts;
     for (int l = 1; l <= NL; ++l) tot += (size_t)(1 + nc) * cells(c->L[l].G);
     if (hipMalloc(&c->init_pool, sizeof(double) * tot) != hipSuccess)
@@ -1688,6 +1693,14 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
     std::vector<long> u(n);
     for (int k = 0; k < n; ++k) u[k] = cells(geom(k, 0));
     rb.add(&b->w_cells0, u, kBlock);
+    {
+        std::vector<long> bs(n);
+        long slots = 0;
+        for (int k = 0; k < n; ++k) slots += blu_slots(grids[k].nx, grids[k].ny, false);
+        b->blu_patch = blu_patches(b->dim, slots);
+        for (int k = 0; k < n; ++k) bs[k] = blu_slots(grids[k].nx, grids[k].ny, b->blu_patch);
+        rb.add(&b->w_blu, bs, kBlock);
+    }
     std::vector<int> roff(n), rcnt(n);
     {
         long pos = 0;
@@ -1872,16 +1885,14 @@ int nmg_batch_newton_mg_solve(nmg_batch *b, const double *const *z, double *cons
     std::vector<double> res(n, 0.0), res0(n, 0.0);
     int nactive = n;
     BHIPCHK(b, launch_b_threshold(dim, b->d_inst, b->w_cells0, b->d_active, b->stream));
-    int ti256 = 0;
-    while (kTileChoices[ti256] != kBlock) ++ti256;
     int it = 0;
     for (it = 0; it < p.max_newton && nactive > 0; ++it) {
         BHIPCHK(b, launch_b_copy_state(dim, b->d_inst, b->w_cells0, b->d_active, 0, b->stream));
         const int order[4] = {0, 1, 1, 0};
         for (int s = 0; s < p.blu_sweeps; ++s)
             for (int q = 0; q < 4; ++q)
-                BHIPCHK(b, launch_b_blu_half(dim, p.flux, b->d_inst, b->w_plane[0][ti256], b->d_active,
-                                             order[q], b->stream));
+                BHIPCHK(b, launch_b_blu_half(dim, p.flux, b->d_inst, b->w_blu, b->d_active,
+                                             order[q], b->blu_patch, b->stream));
         BHIPCHK(b, launch_b_isolated(dim, b->d_inst, b->w_cells0, b->d_active, b->stream));
         BHIPCHK(b, launch_b_assemble(dim, p.flux, b->f32, b->d_inst, b->w_cells0, b->d_active,
                                      b->d_partial, b->stream));

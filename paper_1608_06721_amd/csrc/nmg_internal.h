@@ -178,6 +178,10 @@ hipError_t launch_blu_half_io(const Phys &P, const double *z, const double *Uown
                               hipStream_t s, const int *gate, const StopTest &test,
                               double *res_partial);
 int blu_half_blocks(const Phys &P, int lanes);
+// Order (patches or rows) of the one-lane kernels' slots for a launch of that
+// many cells per colour, and the slot numbers of one colour in either order.
+bool blu_patches(int dim, long slots);
+long blu_slots(int nx, int ny, bool patch);
 // n symmetric BLU-SGS sweeps (half sweeps of colours 0, 1, 1, 0 each), runs
 // of one colour merged into single launches: 0, 1 x2, 0 for one sweep.  The
 // stop test, if any, is done by the first launch.
@@ -310,7 +314,7 @@ hipError_t launch_b_count_iso(const BatchInst *bi, WorkRange w, const int *activ
 hipError_t launch_b_reduce(const double *partial, const int *off, const int *cnt, int n,
                            const int *active, double *out, hipStream_t s);
 hipError_t launch_b_blu_half(int dim, int flux, const BatchInst *bi, WorkRange w,
-                             const int *active, int color, hipStream_t s);
+                             const int *active, int color, bool patch, hipStream_t s);
 // Fused half-sweep pair of launch_sgs_pair over a work list of 32x16 tiles
 // (2D): flip 0 reads the second colour from x and writes it to xt, flip 1
 // the reverse.

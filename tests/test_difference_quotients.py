@@ -108,3 +108,27 @@ def test_assembly_and_sweep(dim, flux, kind, monkeypatch):
             ctx.blu_sweep(dev(z), V)
             same(V, Uo, "U after a sweep, %s lanes" % lanes)
             ctx.close()
+
+
+# Inflow sides on every side of the grid, in both slot orders and with waves
+# that are full, ragged and nearly empty: the celerities of a wave's boundary
+# cells are formed together.
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(2, 2), (5, 3), (130, 66), (63, 129), (1030, 520)])
+@pytest.mark.parametrize("qn", [0.8, 1e-3, 1e70])
+def test_inflow_sides(nx, ny, qn, monkeypatch):
+    from paper_1608_06721_amd import nmg
+    z, U = W.random_state(2, nx, ny, 5)
+    for bc in ([W.open_q(qn, 0.1), W.open_h(1.1), W.open_q(qn), W.open_q(qn, 0.0)],
+               [W.open_h(1.0), W.open_q(qn), W.wall(W.SLIP), (W.OPEN, 0.9, qn, 0.2)]):
+        prob = W.Problem("in", 2, nx, ny, 0.0, 5.0, 0.0, 3.0, bc, W.default_params(2, n_levels=0),
+                         z, U)
+        print("[inflow]", nx, ny, qn, flush=True)
+        monkeypatch.setenv("NMG_BLU_LANES", "1")
+        ctx = nmg.Context.from_problem(prob)
+        V = dev(U)
+        ctx.blu_sweep(dev(z), V)
+        same(V, oracle.blu_sweep(prob, U), "U after a sweep")
+        ctx.assemble_residual_jacobian(dev(z), dev(U), want_norm=False)
+        same(ctx.get_system(0)[0], oracle.assemble(prob, U)[0], "A")
+        ctx.close()

@@ -146,8 +146,8 @@ typedef struct {
  *                     one lane in its runs of half sweeps (default: two
  *                     lanes per cell in 2D where the level has at most 128
  *                     cells per colour);
- *   NMG_FUSE          most half sweeps per launch on the launched coarse
- *                     levels: 3 (default), 2 or 1;
+ *   NMG_FUSE          most half sweeps per launch on the launched levels small
+ *                     enough for runs of them: 5 (default) down to 1;
  *   NMG_BLU_LANES     lanes per cell of every BLU-SGS half sweep (Step 1 and
  *                     Step 2.1): 1, 4 (one per evaluation of the forward
  *                     differences) or 16 (one per face and evaluation, 2D;

@@ -35,7 +35,8 @@ enum ColorState {
 struct Level {
     LevelGeom G;
     void *A = nullptr, *b = nullptr, *x = nullptr;   // double, or float (FP32 inner)
-    void *xt = nullptr;     // one colour's planes: the other buffer of fused half-sweep pairs
+    void *xt = nullptr;     // the other buffer of x (runs of half sweeps; the two change places)
+    int flip = 0;           // batches: the current x of every instance is in its xt
     int st[2] = {ST_ZERO, ST_ZERO};
     int last = -1;      // colour of the last half sweep if nothing changed since, else -1
 };
@@ -52,7 +53,8 @@ struct nmg_ctx {
     Phys P;
     int dim = 0, nc = 0, nb = 0, ne = 0, NL = 0;
     bool f32 = false;                 // FP32 inner V-cycle
-    int fuse = 3;                     // most half sweeps per launch on launched coarse levels
+    int fuse = kRunMax;               // most half sweeps per launch
+    bool restricted = false;          // the last smoothing also restricted its residual
     int split = 1;                    // coarsest-level runs may use two lanes per cell
     int blu_lanes = -1;               // lanes per cell of BLU-SGS half sweeps (-1: by mesh)
     int step1_graph = 1;              // Step 1 runs of kStep1Ahead sweeps replayed as graphs
@@ -129,8 +131,8 @@ struct nmg_batch {
     WorkRange w_plane[kMaxLevels][kNumTiles];   // colour-plane tiles per tile length
     WorkRange w_ccells[kMaxLevels];       // 256-cell tiles of level l (Galerkin into l)
     WorkRange w_rchild[kMaxLevels];       // tiles of 256 children of level l's cells (restriction into l)
-    WorkRange w_tile2d[kMaxLevels];       // 32x16 cell tiles of level l (fused half-sweep pairs)
-    long cells_l[kMaxLevels] = {};        // cells of level l summed over the instances
+    WorkRange w_run[kMaxLevels];          // tiles of level l's runs of half sweeps
+    int run_tx[kMaxLevels] = {};          // their width, 0: single launches
     int tile[kMaxLevels];                 // tile length of the half sweeps per level
     int persist = 0;                      // blocks of the persistent half sweep (0: one per item)
     int *d_active = nullptr, *h_active = nullptr;   // instances still iterating
@@ -217,6 +219,13 @@ int check_params(const nmg_grid *g, const nmg_bc *bc, const nmg_params *p, std::
 
 // ---- multigrid on the colour-split hierarchy -----------------------------
 
+// Where a batch's current x of level l and of the next coarser level are
+// (the flip bits of the batched launchers).
+int batch_flip(const nmg_ctx *c, int l)
+{
+    return c->L[l].flip | (l < c->NL ? c->L[l + 1].flip << 1 : 0);
+}
+
 // res: a restriction from level l follows this half sweep; a normal-mode
 // launch then also writes the updated cells' residuals (c->rres), which the
 // restriction reads instead of recomputing them.  Any other change to the
@@ -249,13 +258,13 @@ int halfsweep(nmg_ctx *c, int l, int color, bool res = false)
         while (kTileChoices[ti] != tl) ++ti;
         if (res) {
             HIPCHK(c, launch_b_sgs_half_res(c->dim, c->f32, tl, B->d_lv + (long)l * B->n,
-                                            B->w_plane[l][ti], B->d_active, color, c->stream));
+                                            B->w_plane[l][ti], B->d_active, color, batch_flip(c, l), c->stream));
             c->res_level = l;
             c->res_color = color;
         } else {
             HIPCHK(c, launch_b_sgs_half(c->dim, c->f32, mode, tl, B->d_lv + (long)l * B->n,
                                         B->w_plane[l][ti], B->d_active, color, B->persist,
-                                        c->stream));
+                                        batch_flip(c, l), c->stream));
         }
         Lv.st[color] = ST_VALID;
         Lv.last = color;
@@ -300,24 +309,16 @@ int halfsweep(nmg_ctx *c, int l, int color, bool res = false)
 
 int smooth_single(nmg_ctx *c, int l, int iters, bool res_last = false);
 
-// Whether the half sweeps of level l are launched as fused pairs: 2D levels
-// launched level by level whose half sweep is bound by launch latency rather
-// than bandwidth (measured: a pair takes 6.7-8.0 us against 2 x 4.6-4.8 us
-// up to 256x256, 21.5 us against 2 x 10.3 us at 512x512).
-constexpr long kPairMaxCells = 1L << 17;
-// Triples replace a pair and a single launch only on the smallest launched
-// levels (measured: 9.4 us against 6.5 + 4.5 us at 64x64, 11.8 against
-// 7.0 + 4.7 us at 128x128, 13.5 against 8.0 + 4.8 us at 256x256).
-constexpr long kTripleMaxCells = 1L << 12;
-long batch_cells(const nmg_ctx *c, int l) { return c->batch->cells_l[l]; }
-
-bool fuse_pairs(const nmg_ctx *c, int l)
+// Tile width of level l's runs of half sweeps, 0 where its half sweeps are
+// launched one by one (run_tile_x; never while recording, on levels of the
+// coarse kernel, on a batch's finest level or, with the timing hook on, on the
+// finest level, whose single launches it times).
+int run_width(const nmg_ctx *c, int l)
 {
-    if (c->recording || c->dim != 2 || l == 0) return false;
-    if (c->lc >= 0 && l >= c->lc) return false;
-    const long n = c->batch ? batch_cells(c, l) : cells(c->L[l].G);
-    if (n > kPairMaxCells) return false;
-    return c->fuse >= 2;
+    if (c->recording || c->dim != 2 || c->fuse < 2) return 0;
+    if (c->lc >= 0 && l >= c->lc) return 0;
+    if (l == 0 && c->timing) return 0;
+    return c->batch ? c->batch->run_tx[l] : run_tile_x(cells(c->L[l].G), c->f32);
 }
 
 int sweep_mode(int st_other)
@@ -331,86 +332,53 @@ int sweep_mode(int st_other)
 }
 
 // The half sweeps of `iters` symmetric iterations on level l (colour order
-// 0, 1, 1, 0, a repeat of the last colour elided), fused into launches of two
-// or three consecutive half sweeps.  Fused launches come in groups of two
-// (pair + pair or pair + triple) that start on the same colour: the first
-// reads the second colour from x and writes it to the level's xt, the second
-// reads it from xt and writes it back to x, so the values end in x.  The
-// rest are launched one by one; the plan uses the fewest launches.
-int smooth_pairs(nmg_ctx *c, int l, int iters)
+// 0, 1, 1, 0, a repeat of the last colour elided) in runs of at most c->fuse,
+// as even as they go, a run of one as a single launch.  The last run also
+// restricts the residual where a restriction follows (c->restricted).
+int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, int tx)
 {
     Level &Lv = c->L[l];
     const Level &Lc = c->L[l + 1 <= c->NL ? l + 1 : l];
-    constexpr int kMax = 64;
-    int col[kMax], mode[kMax], k = 0;
-    int st[2] = {Lv.st[0], Lv.st[1]}, last = Lv.last;
-    const int order[4] = {0, 1, 1, 0};
-    for (int it = 0; it < iters; ++it)
-        for (int q = 0; q < 4; ++q) {
-            const int cl = order[q];
-            if (cl == last) continue;
-            if (k == kMax) return smooth_single(c, l, iters);
-            col[k] = cl;
-            mode[k] = sweep_mode(st[cl ^ 1]);
-            st[cl] = ST_VALID;
-            last = cl;
-            ++k;
-        }
-    // best[q]: fewest launches for half sweeps q..k-1; step[q]: 1 (single),
-    // 4 (pair + pair) or 5 (pair + triple)
-    int best[kMax + 1], step[kMax + 1];
-    const bool triples = !c->batch && c->fuse >= 3 && cells(Lv.G) <= kTripleMaxCells;
-    best[k] = 0;
-    for (int q = k - 1; q >= 0; --q) {
-        best[q] = 1 + best[q + 1];
-        step[q] = 1;
-        if (q + 4 <= k && 2 + best[q + 4] < best[q]) { best[q] = 2 + best[q + 4]; step[q] = 4; }
-        if (triples && q + 5 <= k && 2 + best[q + 5] < best[q]) {
-            best[q] = 2 + best[q + 5];
-            step[q] = 5;
-        }
-    }
-    const size_t esz = c->f32 ? sizeof(float) : sizeof(double);
-    for (int q = 0; q < k;) {
-        if (step[q] == 1) {
-            int rc = halfsweep(c, l, col[q]);
+    const int first = (Lv.last == 0) ? 1 : 0;
+    const long total = iters > 0 ? 2L * iters + 1 - first : 0;
+    const long runs = (total + c->fuse - 1) / c->fuse;
+    int color = first;
+    for (long q = 0; q < runs; ++q) {
+        const int count = (int)(total / runs + (q < total % runs));
+        const bool last = q + 1 == runs;
+        if (count == 1) {
+            int rc = halfsweep(c, l, color, last && res_last);
             if (rc) return rc;
-            ++q;
-            continue;
-        }
-        const int c1 = col[q], c2 = c1 ^ 1;
-        if (c->batch) {
-            const nmg_batch *B = c->batch;
-            const BatchLevel *blv = B->d_lv + (long)l * B->n;
-            HIPCHK(c, launch_b_sgs_pair(c->f32, mode[q], blv, B->w_tile2d[l], B->d_active, c1, 0,
-                                        c->stream));
-            HIPCHK(c, launch_b_sgs_pair(c->f32, MODE_NORMAL, blv, B->w_tile2d[l], B->d_active, c1,
-                                        1, c->stream));
+        } else {
+            if (c->res_level == l) c->res_level = -1;
+            const int mode = sweep_mode(Lv.st[color ^ 1]);
+            const bool res = last && res_last;
+            if (c->batch) {
+                const nmg_batch *B = c->batch;
+                HIPCHK(c, launch_b_sgs_run(c->f32, tx, mode, res, B->d_lv + (long)l * B->n,
+                                           B->w_run[l], B->d_active, count, color,
+                                           batch_flip(c, l), c->stream));
+                if (mode != MODE_ZERO) Lv.flip ^= 1;
+            } else {
+                HIPCHK(c, launch_sgs_run(c->f32, tx, mode, Lv.G, Lv.A, Lv.b, Lv.x,
+                                         mode == MODE_ZERO ? Lv.x : Lv.xt, count, color, Lc.G,
+                                         Lc.x, res ? Lc.b : nullptr, c->stream));
+                if (mode != MODE_ZERO) std::swap(Lv.x, Lv.xt);
+            }
             Lv.st[0] = Lv.st[1] = ST_VALID;
-            Lv.last = c2;
-            q += 4;
-            continue;
+            Lv.last = color ^ ((count - 1) & 1);
+            c->restricted = res;
         }
-        void *xc2 = (char *)Lv.x + (size_t)c2 * c->nc * Lv.G.plane * esz;
-        HIPCHK(c, launch_sgs_pair(c->f32, mode[q], Lv.G, Lv.A, Lv.b, Lv.x, xc2, Lv.xt, c1,
-                                  Lc.G, Lc.x, c->stream));
-        if (step[q] == 4)
-            HIPCHK(c, launch_sgs_pair(c->f32, MODE_NORMAL, Lv.G, Lv.A, Lv.b, Lv.x, Lv.xt, xc2,
-                                      c1, Lc.G, Lc.x, c->stream));
-        else
-            HIPCHK(c, launch_sgs_triple(c->f32, MODE_NORMAL, Lv.G, Lv.A, Lv.b, Lv.x, Lv.xt, xc2,
-                                        c1, Lc.G, Lc.x, c->stream));
-        Lv.st[0] = Lv.st[1] = ST_VALID;
-        Lv.last = step[q] == 4 ? c2 : c1;
-        q += step[q];
+        color ^= count & 1;
     }
     return NMG_OK;
 }
 
-// res_last: a restriction from level l follows (see halfsweep).
+// res_last: a restriction from level l follows (see halfsweep, smooth_runs).
 int smooth(nmg_ctx *c, int l, int iters, bool res_last = false)
 {
-    if (fuse_pairs(c, l)) return smooth_pairs(c, l, iters);
+    c->restricted = false;
+    if (const int tx = run_width(c, l)) return smooth_runs(c, l, iters, res_last, tx);
     return smooth_single(c, l, iters, res_last);
 }
 
@@ -446,7 +414,8 @@ int materialize(nmg_ctx *c, int l)
             int ti = 0;
             while (kTileChoices[ti] != kBlock) ++ti;
             HIPCHK(c, launch_b_fix_color(c->dim, c->f32, op, B->d_lv + (long)l * B->n,
-                                         B->w_plane[l][ti], B->d_active, color, c->stream));
+                                         B->w_plane[l][ti], B->d_active, color, batch_flip(c, l),
+                                         c->stream));
         } else {
             HIPCHK(c, launch_fix_color(c->dim, c->f32, op, Lv.G, Lv.x, color, Lc.G, Lc.x, c->stream));
         }
@@ -478,14 +447,17 @@ int cycle(nmg_ctx *c, int l)
         Level &Lc = c->L[l + 1];
         if (c->recording)
             c->rec.push_back(CoarseOp{COP_RESTRICT, l, 0, 0});
+        else if (c->restricted)
+            ;                   // done by the smoothing's last launch
         else if (c->batch && c->res_level == l)
             HIPCHK(c, launch_b_restrict_res(c->dim, c->f32,
                                             c->batch->d_lv + (long)l * c->batch->n,
                                             c->batch->w_rchild[l + 1], c->batch->d_active,
-                                            c->res_color, c->stream));
+                                            c->res_color, batch_flip(c, l), c->stream));
         else if (c->batch)
             HIPCHK(c, launch_b_restrict(c->dim, c->f32, c->batch->d_lv + (long)l * c->batch->n,
-                                        c->batch->w_rchild[l + 1], c->batch->d_active, c->stream));
+                                        c->batch->w_rchild[l + 1], c->batch->d_active,
+                                        batch_flip(c, l), c->stream));
         else if (c->res_level == l)
             HIPCHK(c, launch_restrict_res(c->dim, c->f32, Lv.G, Lv.A, Lv.b, Lv.x, Lc.G, Lc.b,
                                           c->rres, c->res_color,
@@ -1160,6 +1132,10 @@ int nmg_create(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
 
 namespace {
 
+// Whether level l has a second x buffer: the levels small enough for runs of
+// half sweeps (in a batch the sum over its instances decides, so at most those).
+bool has_xt(const nmg_ctx *c, int l) { return c->dim == 2 && run_tile_x(cells(c->L[l].G), c->f32); }
+
 int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params, void *stream,
                bool plan, nmg_ctx **out)
 {
@@ -1181,7 +1157,7 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
     c->P = make_phys(grid, bc, params);
 
     c->f32 = params->inner_fp32 != 0;
-    if (const char *e = std::getenv("NMG_FUSE")) c->fuse = std::atoi(e);
+    if (const char *e = std::getenv("NMG_FUSE")) c->fuse = std::min(std::atoi(e), kRunMax);
     if (const char *e = std::getenv("NMG_COARSE_SPLIT")) c->split = std::atoi(e) != 0;
     if (const char *e = std::getenv("NMG_BLU_LANES")) {
         const int v = std::atoi(e);
@@ -1194,7 +1170,7 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
         int nx = grid->nx >> l, ny = grid->dim == 1 ? 1 : grid->ny >> l;
         c->L[l].G = make_geom(nx, ny);
         total += (size_t)2 * c->ne * c->L[l].G.planeP + (size_t)2 * 2 * c->nc * c->L[l].G.plane +
-                 (l > 0 ? (size_t)c->nc * c->L[l].G.plane : 0);
+                 (has_xt(c, l) ? (size_t)2 * c->nc * c->L[l].G.plane : 0);
     }
     if (plan) total += (size_t)c->nc * c->L[0].G.plane;      // rres (not used by batches)
     char *pool = nullptr;
@@ -1209,9 +1185,9 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
         Lv.A = pool + off * esz; off += (size_t)2 * c->ne * Lv.G.planeP;
         Lv.b = pool + off * esz; off += (size_t)2 * c->nc * Lv.G.plane;
         Lv.x = pool + off * esz; off += (size_t)2 * c->nc * Lv.G.plane;
-        if (l > 0) {      // fused pairs never run on the finest level
+        if (has_xt(c, l)) {
             Lv.xt = pool + off * esz;
-            off += (size_t)c->nc * Lv.G.plane;
+            off += (size_t)2 * c->nc * Lv.G.plane;
         }
     }
     if (plan) {
@@ -1718,12 +1694,15 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
             rb.add(&b->w_ccells[l], u, kBlock);
             for (int k = 0; k < n; ++k) u[k] = cells(geom(k, l)) * (b->dim == 1 ? 2 : 4);
             rb.add(&b->w_rchild[l], u, kBlock);
-            for (int k = 0; k < n; ++k)
-                u[k] = (long)((geom(k, l).nx + kPairTX - 1) / kPairTX) *
-                       ((geom(k, l).ny + kPairTY - 1) / kPairTY);
-            rb.add(&b->w_tile2d[l], u, 1);
         }
-        for (int k = 0; k < n; ++k) b->cells_l[l] += cells(geom(k, l));
+        long total = 0;
+        for (int k = 0; k < n; ++k) total += cells(geom(k, l));
+        if (l >= 1 && b->dim == 2) b->run_tx[l] = run_tile_x(total, b->f32);
+        if (const int tx = b->run_tx[l]) {
+            for (int k = 0; k < n; ++k)
+                u[k] = (long)((geom(k, l).nx + tx - 1) / tx) * ((geom(k, l).ny + kRunTY - 1) / kRunTY);
+            rb.add(&b->w_run[l], u, 1);
+        }
     }
     // residual planes of the last pre-smoothing half sweep, one per instance
     const size_t esz = b->f32 ? sizeof(float) : sizeof(double);
@@ -1744,7 +1723,7 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
             const Level &Lf = b->inst[k]->L[l];
             const Level &Lc = b->inst[k]->L[l < NL ? l + 1 : l];
             blv[(size_t)l * n + k] = BatchLevel{Lf.G, Lc.G, Lf.A, Lf.b, Lf.x, Lc.A, Lc.b, Lc.x,
-                                                Lf.xt, (char *)b->d_rr + rr_off[k]};
+                                                Lf.xt, Lc.xt, (char *)b->d_rr + rr_off[k]};
         }
     b->h_inst.resize(n);
     for (int k = 0; k < n; ++k) {
@@ -1834,7 +1813,7 @@ int nmg_batch_autotune(nmg_batch *b, int reps, int *tiles_out)
             const BatchLevel *lv = b->d_lv + (long)l * b->n;
             auto sweep = [&]() {
                 return launch_b_sgs_half(b->dim, b->f32, MODE_NORMAL, kTileChoices[ti], lv,
-                                         b->w_plane[l][ti], b->d_active, 0, b->persist,
+                                         b->w_plane[l][ti], b->d_active, 0, b->persist, 0,
                                          b->stream);
             };
             float ms = 0.0f;

@@ -65,7 +65,8 @@ enum SweepMode {
 };
 
 constexpr int kBlock = 256;
-constexpr int kPairTX = 32, kPairTY = 16;   // cell tiles of the fused half-sweep pairs
+constexpr int kRunTY = 8;             // rows of the tiles of a run of half sweeps
+constexpr int kRunMax = 5;            // most half sweeps in one run
 constexpr int kCoarseBlock = 512;     // one workgroup runs the coarse part of a cycle
 constexpr int kMaxLevels = 16;
 constexpr int kMaxCoarseOps = 1 << 16;  // longest recorded coarse program
@@ -211,17 +212,15 @@ hipError_t launch_sgs_half_res(int dim, bool f32, const LevelGeom &G, const void
 hipError_t launch_restrict_res(int dim, bool f32, const LevelGeom &G, const void *A,
                                const void *b, const void *x, const LevelGeom &Gc, void *bc,
                                const void *rin, int rcol, bool stream, hipStream_t s);
-// Two consecutive half sweeps (colour `color` in `mode`, then the other colour
-// in normal mode) in one launch, 2D only: colour `color` is updated in x, the
-// other colour is read from xin (NC planes) and written to xout (NC planes).
-hipError_t launch_sgs_pair(bool f32, int mode, const LevelGeom &G, const void *A, const void *b,
-                           void *x, const void *xin, void *xout, int color, const LevelGeom &Gc,
-                           const void *xc, hipStream_t s);
-// Three consecutive half sweeps (colours color, other, color; the first in
-// `mode`) in one launch, 2D only, with the buffers of launch_sgs_pair.
-hipError_t launch_sgs_triple(bool f32, int mode, const LevelGeom &G, const void *A,
-                             const void *b, void *x, const void *xin, void *xout, int color,
-                             const LevelGeom &Gc, const void *xc, hipStream_t s);
+// `count` (2..kRunMax) consecutive half sweeps of alternating colours (colour
+// `color` first, in `mode`) in one launch, 2D only, on tiles run_tile_x cells
+// wide: both colours are read from xin and written to xout (two buffers,
+// except in MODE_ZERO, where xin is not read); with bc the restriction of the
+// resulting residual to the next level follows.
+int run_tile_x(long cells, bool f32);
+hipError_t launch_sgs_run(bool f32, int tx, int mode, const LevelGeom &G, const void *A,
+                          const void *b, const void *xin, void *xout, int count, int color,
+                          const LevelGeom &Gc, const void *xc, void *bc, hipStream_t s);
 hipError_t launch_galerkin(int dim, bool f32, const LevelGeom &Gf, const void *Af,
                            const LevelGeom &Gc, void *Ac, hipStream_t s);
 // Materialize one colour of x: op 0 = set zero, 1 = add the parent's
@@ -280,7 +279,7 @@ struct BatchLevel {
     LevelGeom G, Gc;
     void *A, *b, *x;
     void *Ac, *bc, *xc;
-    void *xt;               // the level's alternate planes for fused half-sweep pairs
+    void *xt, *xct;         // the other buffer of x and of xc (runs of half sweeps)
     void *rr;               // the instance's residual planes (launch_b_sgs_half_res)
 };
 
@@ -315,11 +314,11 @@ hipError_t launch_b_reduce(const double *partial, const int *off, const int *cnt
                            const int *active, double *out, hipStream_t s);
 hipError_t launch_b_blu_half(int dim, int flux, const BatchInst *bi, WorkRange w,
                              const int *active, int color, bool patch, hipStream_t s);
-// Fused half-sweep pair of launch_sgs_pair over a work list of 32x16 tiles
-// (2D): flip 0 reads the second colour from x and writes it to xt, flip 1
-// the reverse.
-hipError_t launch_b_sgs_pair(bool f32, int mode, const BatchLevel *lv, WorkRange w,
-                             const int *active, int color, int flip, hipStream_t s);
+// Batched launch_sgs_run over a work list of tx x kRunTY tiles (2D).  Here and
+// below, flip: bit 0 set where the level's x is in BatchLevel::xt, bit 1 where
+// the next coarser level's is.
+hipError_t launch_b_sgs_run(bool f32, int tx, int mode, bool res, const BatchLevel *lv, WorkRange w,
+                            const int *active, int count, int color, int flip, hipStream_t s);
 hipError_t launch_b_update(int dim, bool f32, const BatchInst *bi, WorkRange w,
                            const int *active, hipStream_t s);
 hipError_t launch_b_threshold(int dim, const BatchInst *bi, WorkRange w, const int *active,
@@ -331,17 +330,17 @@ hipError_t launch_b_copy_state(int dim, const BatchInst *bi, WorkRange w, const 
 // list instead of one block per work item (kb_sgs_half_loop).
 hipError_t launch_b_sgs_half(int dim, bool f32, int mode, int tile, const BatchLevel *lv,
                              WorkRange w, const int *active, int color, int persist,
-                             hipStream_t s);
+                             int flip, hipStream_t s);
 hipError_t launch_b_restrict(int dim, bool f32, const BatchLevel *lv, WorkRange w,
-                             const int *active, hipStream_t s);
+                             const int *active, int flip, hipStream_t s);
 // Batched launch_sgs_half_res / launch_restrict_res (normal mode; each
 // instance's residuals in its BatchLevel::rr).
 hipError_t launch_b_sgs_half_res(int dim, bool f32, int tile, const BatchLevel *lv, WorkRange w,
-                                 const int *active, int color, hipStream_t s);
+                                 const int *active, int color, int flip, hipStream_t s);
 hipError_t launch_b_restrict_res(int dim, bool f32, const BatchLevel *lv, WorkRange w,
-                                 const int *active, int rcol, hipStream_t s);
+                                 const int *active, int rcol, int flip, hipStream_t s);
 hipError_t launch_b_fix_color(int dim, bool f32, int op, const BatchLevel *lv, WorkRange w,
-                              const int *active, int color, hipStream_t s);
+                              const int *active, int color, int flip, hipStream_t s);
 hipError_t launch_b_galerkin(int dim, bool f32, const BatchLevel *lv, WorkRange w,
                              const int *active, hipStream_t s);
 // The coarse-cycle kernel with one workgroup per instance: workgroup k uses

@@ -143,7 +143,7 @@ typedef struct {
  *   NMG_COARSE_REG    0 turns off register-resident runs on that kernel's
  *                     first level (default on);
  *   NMG_COARSE_SPLIT  0 gives every cell of the LDS-resident coarsest level
- *                     one lane in its runs of half sweeps (default: two
+ *                     one lane in its runs of half sweeps (default: four
  *                     lanes per cell in 2D where the level has at most 128
  *                     cells per colour);
  *   NMG_FUSE          most half sweeps per launch on the launched levels small

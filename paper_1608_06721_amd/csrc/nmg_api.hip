@@ -55,7 +55,7 @@ struct nmg_ctx {
     bool f32 = false;                 // FP32 inner V-cycle
     int fuse = kRunMax;               // most half sweeps per launch
     bool restricted = false;          // the last smoothing also restricted its residual
-    int split = 1;                    // coarsest-level runs may use two lanes per cell
+    int split = 1;                    // coarsest-level runs may use four lanes per cell
     int blu_lanes = -1;               // lanes per cell of BLU-SGS half sweeps (-1: by mesh)
     int step1_graph = 1;              // Step 1 runs of kStep1Ahead sweeps replayed as graphs
     Level L[16];
@@ -597,7 +597,7 @@ long lds_levels_bytes(const nmg_ctx *c, int l_lds)
 // run on level l.
 long reg_exchange_bytes(const nmg_ctx *c, int l)
 {
-    return 2L * c->nc * c->L[l].G.plane * (c->f32 ? 4 : 8);
+    return 2L * c->nc * run_plane(c->L[l].G, c->nc) * (c->f32 ? 4 : 8);
 }
 
 // Whether level lc of context c can run as COP_REGRUN with its exchange area

@@ -90,7 +90,7 @@ struct LevelDev {
 // consecutive half sweeps of alternating colour on an LDS-resident level
 // with a thread per cell, the first of them in `mode` (any start mode for
 // COP_REGRUN, normal or zero start for COP_RUN) and the rest normal; for
-// COP_RUN, aux = 1 allows two lanes per cell (3x3 blocks, where the level
+// COP_RUN, aux = 1 allows four lanes per cell (3x3 blocks, where the level
 // has at most kCoarseBlock / 4 cells per colour).
 // COP_REGRUN is the same on a level in global memory with at most one slot
 // per colour and thread, whose block rows stay in registers and whose x
@@ -104,7 +104,7 @@ struct CoarseOp {
     int color;              // SGS / FIX: colour; RUN, REGRUN: colour of the first half sweep
     int mode;               // SGS / RUN / REGRUN: SweepMode; FIX: 0 zero, 1 add parent, 2 set parent
     int count;              // RUN, REGRUN: number of half sweeps
-    int aux;                // REGRUN: 1 if the restriction follows; RUN: 1 allows two lanes per cell
+    int aux;                // REGRUN: 1 if the restriction follows; RUN: 1 allows four lanes per cell
     int lds_off;            // REGRUN: byte offset of the run's x / exchange area in LDS
 };
 
@@ -365,6 +365,13 @@ __host__ __device__ constexpr int inv_entries(int nc) { return nc * nc + 1; }
 __host__ __device__ inline long lds_level_bytes(const LevelGeom &G, int ne, int nc, long esz)
 {
     return (2 * ne * G.planeP + 2 * inv_entries(nc) * G.planeP + 2 * 2 * nc * G.plane) * esz;
+}
+
+// Values of one component and colour of a level's x in LDS during a
+// register-resident run: rows of W + 1, in 2D with a row below and above.
+__host__ __device__ inline long run_plane(const LevelGeom &G, int nc)
+{
+    return (long)(G.W + 1) * (nc == 2 ? 1 : G.ny + 2);
 }
 
 // Layout conversions between the public FP64 layouts and the colour-split

@@ -514,22 +514,24 @@ int build_coarse(nmg_ctx *c)
 
 // Record the operations of the sub-cycle from level lc (which always starts
 // from a zero correction) and upload them with the level table.
-// Replace each maximal sequence of alternating half sweeps on the coarsest
-// level (normal, or zero start first) by one COP_RUN, when that level is in
-// LDS and has a thread per cell in the coarse-cycle kernel.
-void merge_runs(nmg_ctx *c, bool fits)
+// Replace each maximal sequence of alternating half sweeps on a level in LDS
+// that has a thread per cell in the coarse-cycle kernel (fits[level]), the
+// first from stored values or from zero, by one COP_RUN: a run reads the
+// level's rows once, and its half sweeps take 440 (1D) to 820 cycles where one
+// as an operation of its own takes about 2,000.
+void merge_runs(nmg_ctx *c, const bool *fits)
 {
-    const int nl = c->NL;
-    if (c->l_lds < 0 || !fits) return;
+    if (c->l_lds < 0) return;
     std::vector<CoarseOp> out;
     const CoarseOp *r = c->rec.data();
     const int n = (int)c->rec.size();
     for (int q = 0; q < n;) {
         CoarseOp o = r[q];
-        if (o.kind == COP_SGS && o.level == nl && (o.mode == MODE_NORMAL || o.mode == MODE_ZERO)) {
+        if (o.kind == COP_SGS && o.level >= c->l_lds && fits[o.level] &&
+            (o.mode == MODE_NORMAL || o.mode == MODE_ZERO)) {
             int e = q + 1;
-            while (e < n && r[e].kind == COP_SGS && r[e].level == nl && r[e].mode == MODE_NORMAL &&
-                   r[e].color == (r[e - 1].color ^ 1))
+            while (e < n && r[e].kind == COP_SGS && r[e].level == o.level &&
+                   r[e].mode == MODE_NORMAL && r[e].color == (r[e - 1].color ^ 1))
                 ++e;
             o.kind = COP_RUN;
             o.count = e - q;
@@ -657,7 +659,7 @@ void coarse_level_table(const nmg_ctx *c, int l_lds, LevelDev *lv)
 // LDS plan c->l_lds) and upload the operation list.  fits: the coarsest level
 // has a thread per cell (merged runs allowed); reg_ok: level lc's half sweeps
 // may run register-resident with the exchange area at LDS byte rs_off.
-int record_coarse(nmg_ctx *c, bool fits, bool reg_ok, long rs_off)
+int record_coarse(nmg_ctx *c, const bool *fits, bool reg_ok, long rs_off)
 {
     Level saved[16];
     for (int l = 0; l <= c->NL; ++l) saved[l] = c->L[l];
@@ -697,8 +699,9 @@ int plan_coarse(nmg_ctx *c)
     if (c->lc < 0) return NMG_OK;
     c->l_lds = lds_first_level(c, c->lc);
     const long rs_off = (lds_levels_bytes(c, c->l_lds) + 15) / 16 * 16;
-    int rc = record_coarse(c, 2 * c->L[c->NL].G.plane <= kCoarseBlock,
-                           reg_run_fits(c, c->lc, c->l_lds, rs_off), rs_off);
+    bool fits[kMaxLevels];
+    for (int l = 0; l <= c->NL; ++l) fits[l] = 2 * c->L[l].G.plane <= kCoarseBlock;
+    int rc = record_coarse(c, fits, reg_run_fits(c, c->lc, c->l_lds, rs_off), rs_off);
     if (rc || c->lc < 0) return rc;
     LevelDev lv[kMaxLevels];
     coarse_level_table(c, c->l_lds, lv);
@@ -1628,13 +1631,16 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
     }
     if (t->lc >= 0) {
         int l_lds = -2;
-        bool fits = true;
         for (int k = 0; k < n; ++k) {
             const int lk = lds_first_level(b->inst[k], t->lc);
             if (lk < 0) { l_lds = -1; break; }
             l_lds = lk > l_lds ? lk : l_lds;
         }
-        for (int k = 0; k < n; ++k) fits = fits && 2 * geom(k, NL).plane <= kCoarseBlock;
+        bool fits[kMaxLevels];
+        for (int l = 0; l <= NL; ++l) {
+            fits[l] = true;
+            for (int k = 0; k < n; ++k) fits[l] = fits[l] && 2 * geom(k, l).plane <= kCoarseBlock;
+        }
         t->l_lds = l_lds < 0 ? -1 : l_lds;
         long rs_off = 0;
         for (int k = 0; k < n; ++k) {

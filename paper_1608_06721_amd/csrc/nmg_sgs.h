@@ -33,6 +33,16 @@ __device__ __forceinline__ int xcd_block(int b, int n)
     return (k / kXcdChunk) * G + x * kXcdChunk + k % kXcdChunk;
 }
 
+// Column and row of number t in rows of n: 32-bit division (there are fewer
+// than 2^32 cells in any grid whose hierarchy fits a GPU), about a third of
+// the instructions of the 64-bit one.
+__device__ __forceinline__ void split_rows(long t, int n, int &i, int &j)
+{
+    const unsigned u = (unsigned)t, q = u / (unsigned)n;
+    j = (int)q;
+    i = (int)(u - q * (unsigned)n);
+}
+
 // Load of matrix data that one launch reads exactly once, on a level large
 // enough that the host streams it (stream_level).  In FP64 the off-diagonal
 // blocks are then fetched with the non-temporal hint (measured: the
@@ -217,7 +227,8 @@ __device__ __forceinline__ void sgs_cell(const LevelGeom &G, const T *__restrict
     constexpr int NN = NC * NC;
     constexpr int NE = (NF + 1) * NN;
     constexpr int NI = inv_entries(NC);
-    const int j = (int)(t / G.W), k = (int)(t % G.W);
+    int j, k;
+    split_rows(t, G.W, k, j);
     const int i = 2 * k + ((j + color) & 1);
     if (i >= G.nx) return;
     const int oc = color ^ 1;

@@ -152,7 +152,9 @@ typedef struct {
  *                     Step 2.1): 1, 4 (one per evaluation of the forward
  *                     differences) or 16 (one per face and evaluation, 2D;
  *                     4 in 1D); default: 16 in 2D on meshes of at most 2^14
- *                     cells per colour, 4 up to 2^16, else 1.
+ *                     cells per colour, 4 up to 2^16, else 1; left unset,
+ *                     solves also run whole sweeps of 2D meshes of at most
+ *                     4096 cells in one launch each.
  *   NMG_STEP1_GRAPH   0: enqueue every Step 1 launch from the host; default
  *                     1: runs of 64 Step 1 sweeps on a level are captured
  *                     once per context as a HIP graph (on a stream of the

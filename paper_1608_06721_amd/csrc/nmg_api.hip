@@ -917,6 +917,8 @@ int alloc_step1(nmg_ctx *c)
     for (int l = 1; l <= NL; ++l)
         for (int lanes : {1, 4, 16})
             nparts = std::max(nparts, (size_t)blu_half_blocks(level_phys(c, l), lanes));
+    for (int l = 1; l <= NL; ++l)
+        nparts = std::max(nparts, 2 * (size_t)blu_sweep_blocks(level_phys(c, l)));
     size_t tot = nc * c1 + nparts;
     for (int l = 1; l <= NL; ++l) tot += (size_t)(1 + nc) * cells(c->L[l].G);
     if (hipMalloc(&c->init_pool, sizeof(double) * tot) != hipSuccess)
@@ -935,11 +937,33 @@ int alloc_step1(nmg_ctx *c)
 // every run starts at an even sweep index, see step1_sweeps).
 constexpr int kStep1Ahead = 64;
 
-// The three launches of `n` Step 1 sweeps on level l (see nested_init); the
-// first sweep's index on the level is even.
+// Whether a sweep of the mesh of P runs in one launch (unless the lanes per
+// cell are prescribed).
+bool sweep_in_one(const nmg_ctx *c, const Phys &P)
+{
+    return c->blu_lanes < 0 && blu_sweep_blocks(P) > 0;
+}
+
+// The launches of `n` Step 1 sweeps on level l (see nested_init); the first
+// sweep's index on the level is even.
 int step1_sweeps(nmg_ctx *c, int l, int n, hipStream_t s)
 {
     const Phys P = level_phys(c, l);
+    if (sweep_in_one(c, P)) {
+        SweepStop stop;
+        stop.n = blu_sweep_blocks(P);
+        stop.partial[0] = c->init_part;
+        stop.partial[1] = c->init_part + stop.n;
+        stop.max_sweeps = c->prm.init_max_sweeps;
+        stop.thr = std::ldexp(c->prm.eps_p, -l);
+        stop.ctrl = reinterpret_cast<int *>(c->scal + 1);
+        double *buf[2] = {c->Ul[l], c->init_red};
+        for (int k = 0; k < n; ++k) {
+            stop.parity = k & 1;
+            HIPCHK(c, launch_blu_sweep_tile(P, c->zl[l], buf[k & 1], buf[(k & 1) ^ 1], stop, s));
+        }
+        return NMG_OK;
+    }
     const int lanes = c->blu_lanes;
     const double *zl = c->zl[l];
     double *Ul = c->Ul[l], *red = c->init_red;
@@ -1022,16 +1046,19 @@ int nested_init(nmg_ctx *c, const double *z, double *U, int *sweeps, int *level_
     // replayed from a graph per level (the sweep counter is on the device,
     // so the launches of every such run are the same), which spares the host
     // a launch call per kernel: on the small levels those calls took longer
-    // than the kernels.
+    // than the kernels.  The smallest levels run each sweep in one launch
+    // between two buffers (k_blu_sweep_tile), whose stop test is a launch
+    // behind.
     int *ctrl = reinterpret_cast<int *>(c->scal + 1);
     int *h_ctrl = reinterpret_cast<int *>(c->h_scal + 1);
     for (int l = NL; l >= 1; --l) {
         HIPCHK(c, launch_step1_reset(ctrl, c->stream));
+        const bool in_one = sweep_in_one(c, level_phys(c, l));
         int cnt = 0, rc;
         long queued = 0;    // sweeps enqueued on the level
         for (int ahead = 2;; ahead = std::min(2 * ahead, kStep1Ahead)) {
             // the test at sweep index init_max_sweeps stops for certain
-            const long need = (long)c->prm.init_max_sweeps + 1 - queued;
+            const long need = (long)c->prm.init_max_sweeps + (in_one ? 2 : 1) - queued;
             int n = (int)std::min<long>(ahead, std::max<long>(need, 1));
             n += n & 1;
             hipGraphExec_t g = nullptr;
@@ -1060,7 +1087,8 @@ int nested_init(nmg_ctx *c, const double *z, double *U, int *sweeps, int *level_
         *sweeps += cnt;
         if (level_sweeps) level_sweeps[l] = cnt;
         const LevelGeom &Gf = c->L[l - 1].G;
-        HIPCHK(c, launch_inject(c->dim, Gf.nx, Gf.ny, nc, c->Ul[l], l == 1 ? U : c->Ul[l - 1],
+        const double *Uf = in_one && (cnt & 1) ? c->init_red : c->Ul[l];
+        HIPCHK(c, launch_inject(c->dim, Gf.nx, Gf.ny, nc, Uf, l == 1 ? U : c->Ul[l - 1],
                                 c->stream));
     }
     return NMG_OK;
@@ -1349,7 +1377,10 @@ int nmg_newton_mg_solve(nmg_ctx *c, const double *z, double *U, double tol, nmg_
     if ((rc = phase_mark(c, NMG_PHASE_STEP1))) return rc;
     for (n = 0; n < p.max_newton; ++n) {
         HIPCHK(c, hipMemcpyAsync(c->Ulast, U, vbytes, hipMemcpyDeviceToDevice, c->stream));
-        HIPCHK(c, launch_blu_sweeps(c->P, z, U, p.blu_sweeps, c->blu_lanes, c->stream));
+        // (the copy is the other buffer of a sweep in one launch)
+        const int one = p.blu_sweeps > 0 && sweep_in_one(c, c->P);
+        if (one) HIPCHK(c, launch_blu_sweep_tile(c->P, z, c->Ulast, U, SweepStop(), c->stream));
+        HIPCHK(c, launch_blu_sweeps(c->P, z, U, p.blu_sweeps - one, c->blu_lanes, c->stream));
         if ((rc = phase_mark(c, NMG_PHASE_BLU))) return rc;
         if ((rc = assemble(c, z, U, nullptr, &res))) return rc;
         if (st && st->res_hist && n < st->hist_cap) st->res_hist[n] = res;

@@ -183,6 +183,19 @@ int blu_half_blocks(const Phys &P, int lanes);
 // many cells per colour, and the slot numbers of one colour in either order.
 bool blu_patches(int dim, long slots);
 long blu_slots(int nx, int ny, bool patch);
+// A whole sweep in one launch (k_blu_sweep_tile) from Uin to Uout, 2D meshes
+// of at most kSweepTileMaxCells cells; with stop.ctrl as one of Step 1's.
+// blu_sweep_blocks: its blocks (and partials), 0 where it is not used.
+constexpr long kSweepTileMaxCells = 1L << 12;
+struct SweepStop {
+    double *partial[2] = {nullptr, nullptr};    // block sums of ||R_i||_1, by launch parity
+    int n = 0, parity = 0, max_sweeps = 0;
+    double thr = 0.0;
+    int *ctrl = nullptr;    // {stopped, sweeps done, launches by parity}; null: no test
+};
+int blu_sweep_blocks(const Phys &P);
+hipError_t launch_blu_sweep_tile(const Phys &P, const double *z, const double *Uin, double *Uout,
+                                 const SweepStop &stop, hipStream_t s);
 // n symmetric BLU-SGS sweeps (half sweeps of colours 0, 1, 1, 0 each), runs
 // of one colour merged into single launches: 0, 1 x2, 0 for one sweep.  The
 // stop test, if any, is done by the first launch.

@@ -591,7 +591,7 @@ long lds_levels_bytes(const nmg_ctx *c, int l_lds)
     long tot = 0;
     if (l_lds >= 0)
         for (int l = l_lds; l <= c->NL; ++l)
-            tot += lds_level_bytes(c->L[l].G, c->ne, c->nc, c->f32 ? 4 : 8);
+            tot += lds_level_bytes(c->L[l].G, c->nc, c->f32 ? 4 : 8);
     return tot;
 }
 
@@ -634,7 +634,7 @@ int lds_first_level(const nmg_ctx *c, int lc)
     long tot = 0;
     int l_lds = -1;
     for (int l = c->NL; l >= lc; --l) {
-        tot += lds_level_bytes(c->L[l].G, c->ne, c->nc, esz);
+        tot += lds_level_bytes(c->L[l].G, c->nc, esz);
         if (tot > kCoarseLdsBytes) break;
         l_lds = l;
     }
@@ -650,7 +650,7 @@ void coarse_level_table(const nmg_ctx *c, int l_lds, LevelDev *lv)
         lv[l] = LevelDev{Lv.G, Lv.A, Lv.b, Lv.x, -1};
         if (l_lds >= 0 && l >= l_lds && l <= c->NL) {
             lv[l].lds_off = off;
-            off += lds_level_bytes(Lv.G, c->ne, c->nc, c->f32 ? 4 : 8);
+            off += lds_level_bytes(Lv.G, c->nc, c->f32 ? 4 : 8);
         }
     }
 }
@@ -1196,12 +1196,15 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
     }
     if (const char *e = std::getenv("NMG_STEP1_GRAPH")) c->step1_graph = std::atoi(e) != 0;
     const size_t esz = c->f32 ? sizeof(float) : sizeof(double);
+    // every level's blocks start on a 256-byte boundary (16-byte loads)
+    auto aligned = [&](size_t n) { return (n + 256 / esz - 1) / (256 / esz) * (256 / esz); };
     size_t total = 0;   // elements
     for (int l = 0; l <= c->NL; ++l) {
         int nx = grid->nx >> l, ny = grid->dim == 1 ? 1 : grid->ny >> l;
         c->L[l].G = make_geom(nx, ny);
         total += (size_t)2 * c->ne * c->L[l].G.planeP + (size_t)2 * 2 * c->nc * c->L[l].G.plane +
                  (has_xt(c, l) ? (size_t)2 * c->nc * c->L[l].G.plane : 0);
+        total = aligned(total);
     }
     if (plan) total += (size_t)c->nc * c->L[0].G.plane;      // rres (not used by batches)
     char *pool = nullptr;
@@ -1220,6 +1223,7 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
             Lv.xt = pool + off * esz;
             off += (size_t)2 * c->nc * Lv.G.plane;
         }
+        off = aligned(off);
     }
     if (plan) {
         c->rres = pool + off * esz;

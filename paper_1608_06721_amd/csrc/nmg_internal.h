@@ -27,10 +27,20 @@ struct Phys {
 // Geometry of one multigrid level in the colour-split layout: every cell
 // (i, j) lives in colour (i + j) & 1 at slot t = j * W + (i >> 1) of a
 // [ny][W] plane, W = (nx + 1) / 2.  Vectors are [colour][NC][ny][W].
-// Matrices are tiled by 64 slots (one wavefront): [colour][tile][NE][64],
-// entry e = (block * NC + row) * NC + col, so the NE entries that one wave
-// reads in a half sweep form one contiguous NE * 512-byte run.
+// Matrices are tiled by 64 slots (one wavefront) and their entries grouped by
+// 16 bytes (two doubles, four floats): [colour][tile][group][64][entries of a
+// group], so that a lane reads a group with one load and a wave's rows form
+// one contiguous run.  A compute unit takes a vector memory instruction of a
+// wave every 16 cycles whatever its width: 31 B per cycle with 8-byte loads,
+// 59 with 16-byte ones (measured with the levels' rows in L2), which bounds the
+// kernels that keep a small level's rows in registers.  Entries of a row: the
+// off-diagonal blocks W, E, S, N (each row by row), then the diagonal block;
+// the entries that fill no group at its end (the last of a 3x3 block) lie in
+// planes of 64 single entries, so nothing is padded.
 constexpr int kTile = 64;
+constexpr int mat_group(int esz) { return 16 / esz; }
+// Entries of one cell's row (nc components).
+__host__ __device__ constexpr int mat_entries(int nc) { return (nc == 2 ? 3 : 5) * nc * nc; }
 
 struct LevelGeom {
     int nx, ny, W;
@@ -49,8 +59,21 @@ inline LevelGeom make_geom(int nx, int ny)
     return g;
 }
 
-// Offset of entry 0 of slot t's block row in a colour-split tiled matrix
-// with NE entries per row; entry e is at + e * kTile.
+// Offset of slot t's first entry in a colour-split matrix of NE entries a row
+// in groups of GW, and of its entry e.
+__host__ __device__ inline long mat_slot(const LevelGeom &G, int NE, int GW, int color, long t)
+{
+    return (long)color * NE * G.planeP + (t / kTile) * NE * kTile + (t % kTile) * GW;
+}
+__host__ __device__ inline long mat_entry(const LevelGeom &G, int NE, int GW, int color, long t,
+                                          int e)
+{
+    const long tile = (long)color * NE * G.planeP + (t / kTile) * NE * kTile;
+    const int s = (int)(t % kTile);
+    return tile + (e < NE / GW * GW ? e / GW * GW * kTile + s * GW + e % GW : e * kTile + s);
+}
+
+// The same for data of NE entries a row without groups (entry e at + e * kTile).
 __host__ __device__ inline long mat_off(const LevelGeom &G, int NE, int color, long t)
 {
     return (long)color * NE * G.planeP + (t / kTile) * NE * kTile + (t % kTile);
@@ -362,22 +385,17 @@ hipError_t launch_b_coarse_cycle(int dim, bool f32, const CoarseOp *ops, int nop
                                  const LevelDev *lv, int ninst, const int *active, int l_lds,
                                  int nl, hipStream_t s);
 
-// Bytes of one level's blocks, right-hand side and correction (both colours)
-// for the scalar size esz.
-inline long level_bytes(const LevelGeom &G, int ne, int nc, long esz)
-{
-    return (2 * ne * G.planeP + 2 * 2 * nc * G.plane) * esz;
-}
 
 // Entries of a block's precomputed inverse data: the NC x NC cofactors and
 // the reciprocal determinant.
 __host__ __device__ constexpr int inv_entries(int nc) { return nc * nc + 1; }
 
-// Bytes of one level's LDS copy in the coarse-cycle kernel: level_bytes plus
-// the block inverses of both colours, tiled like the blocks.
-__host__ __device__ inline long lds_level_bytes(const LevelGeom &G, int ne, int nc, long esz)
+// Bytes of one level's LDS copy in the coarse-cycle kernel: blocks, block
+// inverses, right-hand side and correction of both colours for the scalar size
+// esz (a multiple of 16 for any level).
+__host__ __device__ inline long lds_level_bytes(const LevelGeom &G, int nc, long esz)
 {
-    return (2 * ne * G.planeP + 2 * inv_entries(nc) * G.planeP + 2 * 2 * nc * G.plane) * esz;
+    return (2 * mat_entries(nc) * G.planeP + 2 * inv_entries(nc) * G.planeP + 2 * 2 * nc * G.plane) * esz;
 }
 
 // Values of one component and colour of a level's x in LDS during a

@@ -43,17 +43,60 @@ __device__ __forceinline__ void split_rows(long t, int n, int &i, int &j)
     i = (int)(u - q * (unsigned)n);
 }
 
-// Load of matrix data that one launch reads exactly once, on a level large
-// enough that the host streams it (stream_level).  In FP64 the off-diagonal
-// blocks are then fetched with the non-temporal hint (measured: the
-// 1024x1024 half sweep runs 13% faster; in FP32, and for the diagonal block
-// and b, the hint is slower or neutral).
-template <class T, bool STREAM>
-__device__ __forceinline__ T ld_once(const T *p)
-{
-    if constexpr (STREAM && sizeof(T) == 8) return __builtin_nontemporal_load(p);
-    else return *p;
-}
+// One cell's stored block row (see kTile): NO off-diagonal entries in NF blocks
+// of NN, then the diagonal block's NN.
+template <class T, int NC>
+struct Row {
+    static constexpr int GW = mat_group(sizeof(T)), NF = (NC == 2) ? 2 : 4, NN = NC * NC;
+    static constexpr int NO = NF * NN, NE = mat_entries(NC);
+    static constexpr int ND = NN / GW * GW;     // diagonal entries in groups
+    static_assert(NO % GW == 0 && NN - ND <= 1, "whole groups and at most one single entry");
+    typedef T Group __attribute__((ext_vector_type(GW)));
+
+    __device__ __forceinline__ static long at(const LevelGeom &G, int color, long t)
+    {
+        return mat_slot(G, NE, GW, color, t);
+    }
+    // Offset of entry e of block f (f == NF: the diagonal block) of slot t.
+    __device__ __forceinline__ static long entry(const LevelGeom &G, int color, long t, int f,
+                                                 int e)
+    {
+        return mat_entry(G, NE, GW, color, t, f * NN + e);
+    }
+    // The diagonal's single entry (if NN > ND), from Am and the slot.
+    __device__ __forceinline__ static int last(long t)
+    {
+        return (NE - 1) * kTile - (int)(t % kTile) * (GW - 1);
+    }
+    // The row of pointer Am = A + at(...): ONCE as data that one launch reads
+    // exactly once (the non-temporal hint; FP64 off-diagonal blocks of a level
+    // large enough that the host streams it, stream_level.  Measured: the
+    // 1024x1024 half sweep runs 13% faster; in FP32, and for the diagonal
+    // block and b, the hint is slower or neutral).
+    template <bool ONCE = false>
+    __device__ __forceinline__ static void off(const T *Am, T *a)
+    {
+#pragma unroll
+        for (int g = 0; g < NO / GW; ++g) {
+            const Group *p = (const Group *)(Am + g * GW * kTile);
+            Group v;
+            if constexpr (ONCE && sizeof(T) == 8) v = __builtin_nontemporal_load(p);
+            else v = *p;
+#pragma unroll
+            for (int q = 0; q < GW; ++q) a[g * GW + q] = v[q];
+        }
+    }
+    __device__ __forceinline__ static void diag(const T *Am, long t, T *D)
+    {
+#pragma unroll
+        for (int g = 0; g < ND / GW; ++g) {
+            const Group v = *(const Group *)(Am + (NO + g * GW) * kTile);
+#pragma unroll
+            for (int q = 0; q < GW; ++q) D[g * GW + q] = v[q];
+        }
+        if (ND < NN) D[NN - 1] = Am[last(t)];
+    }
+};
 
 // Solve the NC x NC block system D x = r in precision T: adjugate (cofactors
 // along row 0) times the reciprocal determinant; x = 0 when that reciprocal
@@ -163,18 +206,18 @@ __device__ __forceinline__ void read_other(const LevelGeom &G, const T *xo, int 
 
 // The arithmetic of one block Gauss-Seidel cell update: acc = sum over the
 // neighbours (W, E, S, N order) and components of A_f x_f, then
-// x_i = D_i^-1 (b_i - acc) by solve_block (a holds D) or solve_inv (inv).
+// x_i = D_i^-1 (b_i - acc) by solve_block (D) or solve_inv (inv).  a: the
+// off-diagonal blocks.
 // ZERO: every neighbour value is zero, so acc = 0.  A face without a
 // neighbour has a zero block and a zero value here, so its terms are +0 and
 // leave acc unchanged (acc starts at +0 and can never become -0): it is
 // summed like the others, without a branch.  Each row's sum runs in face,
 // then component order; the rows are interleaved.
 template <class T, int NC, bool ZERO, bool INV>
-__device__ __forceinline__ void gs_update(const T *a, const T *inv, const T *bv,
-                                          const T (*v)[NC], const bool *ok, T *xi)
+__device__ __forceinline__ void gs_update(const T *a, const T *D, const T *inv, const T *bv,
+                                          const T (*v)[NC], T *xi)
 {
     constexpr int NF = (NC == 2) ? 2 : 4;
-    (void)ok;
     T acc[NC];
 #pragma unroll
     for (int r = 0; r < NC; ++r) acc[r] = T(0);
@@ -185,7 +228,7 @@ __device__ __forceinline__ void gs_update(const T *a, const T *inv, const T *bv,
 #pragma unroll
             for (int r = 0; r < NC; ++r)
 #pragma unroll
-                for (int c = 0; c < NC; ++c) p[r][c] = a[((f + 1) * NC + r) * NC + c] * v[f][c];
+                for (int c = 0; c < NC; ++c) p[r][c] = a[(f * NC + r) * NC + c] * v[f][c];
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -198,7 +241,7 @@ __device__ __forceinline__ void gs_update(const T *a, const T *inv, const T *bv,
     if (INV)
         solve_inv<T, NC>(inv, rhs, xi);
     else
-        solve_block<T, NC>(a, rhs, xi);
+        solve_block<T, NC>(D, rhs, xi);
 }
 
 // Block Gauss-Seidel half sweep of one colour: x_i = D_i^-1 (b_i - sum_j
@@ -208,7 +251,7 @@ __device__ __forceinline__ void gs_update(const T *a, const T *inv, const T *bv,
 // before any arithmetic, so each wave keeps ~50 independent loads in flight.
 // INV: the diagonal block is applied through its precomputed inverse data
 // Ai (tiled like A, inv_entries(NC) entries per slot) instead of solve_block.
-// STREAM: off-diagonal blocks loaded through ld_once.
+// STREAM: off-diagonal blocks loaded as read-once data (Row::off).
 // RES (normal mode, INV false): also write the cell's linear residual after
 // its update, b_i - (D_i x_i + sum over existing faces A_ij x_j) in the
 // order of the restriction's residual, to rout (NC planes of the colour's
@@ -223,16 +266,15 @@ __device__ __forceinline__ void sgs_cell(const LevelGeom &G, const T *__restrict
                                          T *__restrict__ rout = nullptr)
 {
     static_assert(!RES || (MODE == MODE_NORMAL && !INV), "residual output needs D and x_j");
-    constexpr int NF = (NC == 2) ? 2 : 4;
-    constexpr int NN = NC * NC;
-    constexpr int NE = (NF + 1) * NN;
+    using R = Row<T, NC>;
+    constexpr int NF = R::NF, NN = R::NN;
     constexpr int NI = inv_entries(NC);
     int j, k;
     split_rows(t, G.W, k, j);
     const int i = 2 * k + ((j + color) & 1);
     if (i >= G.nx) return;
     const int oc = color ^ 1;
-    const T *Am = A + mat_off(G, NE, color, t);
+    const T *Am = A + R::at(G, color, t);
     const T *bm = b + (long)color * NC * G.plane + t;
     const T *xo = x + (long)oc * NC * G.plane;
 
@@ -247,20 +289,18 @@ __device__ __forceinline__ void sgs_cell(const LevelGeom &G, const T *__restrict
         else if (f == FS) { nj[f] = j - 1; ok[f] = j > 0; }
         else { nj[f] = j + 1; ok[f] = j + 1 < G.ny; }
     }
-    T a[NE], bv[NC], v[NF][NC], inv[NI];
+    T a[R::NO], D[NN], bv[NC], v[NF][NC], inv[NI];
     if (INV) {
         const T *Im = Ai + mat_off(G, NI, color, t);
 #pragma unroll
         for (int e = 0; e < NI; ++e) inv[e] = Im[e * kTile];
     } else {
-#pragma unroll
-        for (int e = 0; e < NN; ++e) a[e] = Am[e * kTile];
+        R::diag(Am, t, D);
     }
 #pragma unroll
     for (int r = 0; r < NC; ++r) bv[r] = bm[r * G.plane];
     if (MODE != MODE_ZERO) {
-#pragma unroll
-        for (int e = NN; e < NE; ++e) a[e] = ld_once<T, STREAM>(&Am[e * kTile]);
+        R::template off<STREAM>(Am, a);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             if (ok[f]) {
@@ -272,7 +312,7 @@ __device__ __forceinline__ void sgs_cell(const LevelGeom &G, const T *__restrict
         }
     }
     T xi[NC];
-    gs_update<T, NC, MODE == MODE_ZERO, INV>(a, inv, bv, v, ok, xi);
+    gs_update<T, NC, MODE == MODE_ZERO, INV>(a, D, inv, bv, v, xi);
     T *xm = x + (long)color * NC * G.plane + t;
 #pragma unroll
     for (int r = 0; r < NC; ++r) xm[r * G.plane] = xi[r];
@@ -282,7 +322,7 @@ __device__ __forceinline__ void sgs_cell(const LevelGeom &G, const T *__restrict
         for (int q = 0; q < NC; ++q) {
             acc[q] = T(0);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[q] = acc[q] + a[q * NC + c] * xi[c];
+            for (int c = 0; c < NC; ++c) acc[q] = acc[q] + D[q * NC + c] * xi[c];
         }
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
@@ -291,7 +331,7 @@ __device__ __forceinline__ void sgs_cell(const LevelGeom &G, const T *__restrict
             for (int q = 0; q < NC; ++q)
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
-                    acc[q] = acc[q] + a[((f + 1) * NC + q) * NC + c] * v[f][c];
+                    acc[q] = acc[q] + a[(f * NC + q) * NC + c] * v[f][c];
         }
 #pragma unroll
         for (int q = 0; q < NC; ++q) rout[q * G.plane + t] = bv[q] - acc[q];

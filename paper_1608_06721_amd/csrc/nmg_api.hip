@@ -131,8 +131,9 @@ struct nmg_batch {
     WorkRange w_plane[kMaxLevels][kNumTiles];   // colour-plane tiles per tile length
     WorkRange w_ccells[kMaxLevels];       // 256-cell tiles of level l (Galerkin into l)
     WorkRange w_rchild[kMaxLevels];       // tiles of 256 children of level l's cells (restriction into l)
-    WorkRange w_run[kMaxLevels];          // tiles of level l's runs of half sweeps
-    int run_tx[kMaxLevels] = {};          // their width, 0: single launches
+    WorkRange w_run[kMaxLevels][2];       // tiles of level l's runs of half sweeps without
+                                          // and with a restriction
+    long run_cells[kMaxLevels] = {};      // cells of all instances
     int tile[kMaxLevels];                 // tile length of the half sweeps per level
     int persist = 0;                      // blocks of the persistent half sweep (0: one per item)
     int *d_active = nullptr, *h_active = nullptr;   // instances still iterating
@@ -307,18 +308,15 @@ int halfsweep(nmg_ctx *c, int l, int color, bool res = false)
     return NMG_OK;
 }
 
-int smooth_single(nmg_ctx *c, int l, int iters, bool res_last = false);
-
-// Tile width of level l's runs of half sweeps, 0 where its half sweeps are
-// launched one by one (run_tile_x; never while recording, on levels of the
-// coarse kernel, on a batch's finest level or, with the timing hook on, on the
-// finest level, whose single launches it times).
-int run_width(const nmg_ctx *c, int l)
+// Cells that level l's runs of half sweeps go over, 0 where its half sweeps are
+// launched one by one (while recording, on levels of the coarse kernel and, with
+// the timing hook on, on the finest level, whose single launches it times).
+long run_cells(const nmg_ctx *c, int l)
 {
     if (c->recording || c->dim != 2 || c->fuse < 2) return 0;
     if (c->lc >= 0 && l >= c->lc) return 0;
     if (l == 0 && c->timing) return 0;
-    return c->batch ? c->batch->run_tx[l] : run_tile_x(cells(c->L[l].G), c->f32);
+    return c->batch ? c->batch->run_cells[l] : cells(c->L[l].G);
 }
 
 int sweep_mode(int st_other)
@@ -333,15 +331,20 @@ int sweep_mode(int st_other)
 
 // The half sweeps of `iters` symmetric iterations on level l (colour order
 // 0, 1, 1, 0, a repeat of the last colour elided) in runs of at most c->fuse,
-// as even as they go, a run of one as a single launch.  The last run also
-// restricts the residual where a restriction follows (c->restricted).
-int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, int tx)
+// as even as they go, a run of one as a single launch, all single where runs
+// are too short.  The last run also restricts the residual where a restriction
+// follows (c->restricted).
+int smooth_single(nmg_ctx *c, int l, int iters, bool res_last = false);
+
+int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, long ncells)
 {
     Level &Lv = c->L[l];
     const Level &Lc = c->L[l + 1 <= c->NL ? l + 1 : l];
     const int first = (Lv.last == 0) ? 1 : 0;
     const long total = iters > 0 ? 2L * iters + 1 - first : 0;
     const long runs = (total + c->fuse - 1) / c->fuse;
+    if (total && total / runs + (res_last && runs == 1) < run_least(ncells, c->f32))
+        return smooth_single(c, l, iters, res_last);
     int color = first;
     for (long q = 0; q < runs; ++q) {
         const int count = (int)(total / runs + (q < total % runs));
@@ -353,14 +356,15 @@ int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, int tx)
             if (c->res_level == l) c->res_level = -1;
             const int mode = sweep_mode(Lv.st[color ^ 1]);
             const bool res = last && res_last;
+            const RunTile tile = run_tile(ncells, c->f32, res);
             if (c->batch) {
                 const nmg_batch *B = c->batch;
-                HIPCHK(c, launch_b_sgs_run(c->f32, tx, mode, res, B->d_lv + (long)l * B->n,
-                                           B->w_run[l], B->d_active, count, color,
+                HIPCHK(c, launch_b_sgs_run(c->f32, tile, mode, res, B->d_lv + (long)l * B->n,
+                                           B->w_run[l][res], B->d_active, count, color,
                                            batch_flip(c, l), c->stream));
                 if (mode != MODE_ZERO) Lv.flip ^= 1;
             } else {
-                HIPCHK(c, launch_sgs_run(c->f32, tx, mode, Lv.G, Lv.A, Lv.b, Lv.x,
+                HIPCHK(c, launch_sgs_run(c->f32, tile, mode, Lv.G, Lv.A, Lv.b, Lv.x,
                                          mode == MODE_ZERO ? Lv.x : Lv.xt, count, color, Lc.G,
                                          Lc.x, res ? Lc.b : nullptr, c->stream));
                 if (mode != MODE_ZERO) std::swap(Lv.x, Lv.xt);
@@ -378,7 +382,7 @@ int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, int tx)
 int smooth(nmg_ctx *c, int l, int iters, bool res_last = false)
 {
     c->restricted = false;
-    if (const int tx = run_width(c, l)) return smooth_runs(c, l, iters, res_last, tx);
+    if (const long n = run_cells(c, l)) return smooth_runs(c, l, iters, res_last, n);
     return smooth_single(c, l, iters, res_last);
 }
 
@@ -1163,9 +1167,8 @@ int nmg_create(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
 
 namespace {
 
-// Whether level l has a second x buffer: the levels small enough for runs of
-// half sweeps (in a batch the sum over its instances decides, so at most those).
-bool has_xt(const nmg_ctx *c, int l) { return c->dim == 2 && run_tile_x(cells(c->L[l].G), c->f32); }
+// Whether the levels have a second x buffer (runs of half sweeps).
+bool has_xt(const nmg_ctx *c) { return c->dim == 2; }
 
 int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params, void *stream,
                bool plan, nmg_ctx **out)
@@ -1203,7 +1206,7 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
         int nx = grid->nx >> l, ny = grid->dim == 1 ? 1 : grid->ny >> l;
         c->L[l].G = make_geom(nx, ny);
         total += (size_t)2 * c->ne * c->L[l].G.planeP + (size_t)2 * 2 * c->nc * c->L[l].G.plane +
-                 (has_xt(c, l) ? (size_t)2 * c->nc * c->L[l].G.plane : 0);
+                 (has_xt(c) ? (size_t)2 * c->nc * c->L[l].G.plane : 0);
         total = aligned(total);
     }
     if (plan) total += (size_t)c->nc * c->L[0].G.plane;      // rres (not used by batches)
@@ -1219,7 +1222,7 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
         Lv.A = pool + off * esz; off += (size_t)2 * c->ne * Lv.G.planeP;
         Lv.b = pool + off * esz; off += (size_t)2 * c->nc * Lv.G.plane;
         Lv.x = pool + off * esz; off += (size_t)2 * c->nc * Lv.G.plane;
-        if (has_xt(c, l)) {
+        if (has_xt(c)) {
             Lv.xt = pool + off * esz;
             off += (size_t)2 * c->nc * Lv.G.plane;
         }
@@ -1738,11 +1741,12 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
         }
         long total = 0;
         for (int k = 0; k < n; ++k) total += cells(geom(k, l));
-        if (l >= 1 && b->dim == 2) b->run_tx[l] = run_tile_x(total, b->f32);
-        if (const int tx = b->run_tx[l]) {
+        b->run_cells[l] = total;
+        for (int res = 0; res < 2 && b->dim == 2; ++res) {
+            const RunTile t = run_tile(total, b->f32, res);
             for (int k = 0; k < n; ++k)
-                u[k] = (long)((geom(k, l).nx + tx - 1) / tx) * ((geom(k, l).ny + kRunTY - 1) / kRunTY);
-            rb.add(&b->w_run[l], u, 1);
+                u[k] = (long)((geom(k, l).nx + t.x - 1) / t.x) * ((geom(k, l).ny + t.y - 1) / t.y);
+            rb.add(&b->w_run[l][res], u, 1);
         }
     }
     // residual planes of the last pre-smoothing half sweep, one per instance
@@ -1770,7 +1774,7 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
     for (int k = 0; k < n; ++k) {
         nmg_ctx *c = b->inst[k];
         b->h_inst[k] = BatchInst{c->P, c->L[0].G, nullptr, nullptr, c->Ulast, c->iso,
-                                 c->L[0].A, c->L[0].b, c->L[0].x};
+                                 c->L[0].A, c->L[0].b, c->L[0].x, c->L[0].xt};
     }
     bool ok = hipMalloc(&b->d_work, sizeof(WorkItem) * rb.items.size()) == hipSuccess &&
               hipMalloc(&b->d_lv, sizeof(BatchLevel) * blv.size()) == hipSuccess &&
@@ -1957,7 +1961,8 @@ int nmg_batch_newton_mg_solve(nmg_batch *b, const double *const *z, double *cons
         for (int m = 0; m < p.n_mg; ++m)
             if ((rc = bctx(b, cycle(t, 0)))) return rc;
         if ((rc = bctx(b, materialize(t, 0)))) return rc;
-        BHIPCHK(b, launch_b_update(dim, b->f32, b->d_inst, b->w_cells0, b->d_active, b->stream));
+        BHIPCHK(b, launch_b_update(dim, b->f32, b->d_inst, b->w_cells0, b->d_active,
+                                   t->L[0].flip, b->stream));
     }
     // instances that used every Newton step: residual of the final state
     if (nactive > 0) {

@@ -88,7 +88,6 @@ enum SweepMode {
 };
 
 constexpr int kBlock = 256;
-constexpr int kRunTY = 8;             // rows of the tiles of a run of half sweeps
 constexpr int kRunMax = 5;            // most half sweeps in one run
 constexpr int kCoarseBlock = 512;     // one workgroup runs the coarse part of a cycle
 constexpr int kMaxLevels = 16;
@@ -249,12 +248,17 @@ hipError_t launch_restrict_res(int dim, bool f32, const LevelGeom &G, const void
                                const void *b, const void *x, const LevelGeom &Gc, void *bc,
                                const void *rin, int rcol, bool stream, hipStream_t s);
 // `count` (2..kRunMax) consecutive half sweeps of alternating colours (colour
-// `color` first, in `mode`) in one launch, 2D only, on tiles run_tile_x cells
-// wide: both colours are read from xin and written to xout (two buffers,
-// except in MODE_ZERO, where xin is not read); with bc the restriction of the
-// resulting residual to the next level follows.
-int run_tile_x(long cells, bool f32);
-hipError_t launch_sgs_run(bool f32, int tx, int mode, const LevelGeom &G, const void *A,
+// `color` first, in `mode`) in one launch, 2D only, on run_tile tiles: both
+// colours are read from xin and written to xout (two buffers, except in
+// MODE_ZERO, where xin is not read); with bc the restriction of the resulting
+// residual to the next level follows.  run_tile: the tiles of such a run, with
+// or without the restriction, on a level of `cells` cells (of all instances in
+// a batch); run_least: the fewest half sweeps, a restriction counted as one,
+// that are faster as a run than one by one.
+struct RunTile { int x, y; };
+RunTile run_tile(long cells, bool f32, bool res);
+int run_least(long cells, bool f32);
+hipError_t launch_sgs_run(bool f32, RunTile tile, int mode, const LevelGeom &G, const void *A,
                           const void *b, const void *xin, void *xout, int count, int color,
                           const LevelGeom &Gc, const void *xc, void *bc, hipStream_t s);
 hipError_t launch_galerkin(int dim, bool f32, const LevelGeom &Gf, const void *Af,
@@ -306,7 +310,7 @@ struct BatchInst {
     const double *z;
     double *U, *Ulast;
     unsigned char *iso;
-    void *A, *b, *x;            // level-0 hierarchy arrays
+    void *A, *b, *x, *xt;       // level-0 hierarchy arrays
 };
 
 // One instance of a batch at multigrid level l: the level, the next coarser
@@ -350,13 +354,14 @@ hipError_t launch_b_reduce(const double *partial, const int *off, const int *cnt
                            const int *active, double *out, hipStream_t s);
 hipError_t launch_b_blu_half(int dim, int flux, const BatchInst *bi, WorkRange w,
                              const int *active, int color, bool patch, hipStream_t s);
-// Batched launch_sgs_run over a work list of tx x kRunTY tiles (2D).  Here and
+// Batched launch_sgs_run over a work list of such tiles (2D).  Here and
 // below, flip: bit 0 set where the level's x is in BatchLevel::xt, bit 1 where
 // the next coarser level's is.
-hipError_t launch_b_sgs_run(bool f32, int tx, int mode, bool res, const BatchLevel *lv, WorkRange w,
+hipError_t launch_b_sgs_run(bool f32, RunTile tile, int mode, bool res, const BatchLevel *lv, WorkRange w,
                             const int *active, int count, int color, int flip, hipStream_t s);
+// flip: as bit 0 above, of level 0.
 hipError_t launch_b_update(int dim, bool f32, const BatchInst *bi, WorkRange w,
-                           const int *active, hipStream_t s);
+                           const int *active, int flip, hipStream_t s);
 hipError_t launch_b_threshold(int dim, const BatchInst *bi, WorkRange w, const int *active,
                               hipStream_t s);
 // dir 0: Ulast = U, dir 1: U = Ulast.

@@ -772,9 +772,9 @@ int kbuffers(nmg_ctx *c, int m)
     bool ok = hipMalloc(&c->kV, vb * (m + 1)) == hipSuccess && hipMalloc(&c->kg, vb) == hipSuccess &&
               hipMalloc(&c->kx, vb) == hipSuccess && hipMalloc(&c->kw, vb) == hipSuccess &&
               hipMalloc(&c->kpart, sizeof(double) * (size_t)(m + 1) * nblocks(n)) == hipSuccess &&
-              hipMalloc(&c->kdots, sizeof(double) * (m + 1)) == hipSuccess &&
+              hipMalloc(&c->kdots, sizeof(double) * (2 * m + 3)) == hipSuccess &&
               hipMalloc(&c->kcoef, sizeof(double) * (m + 1)) == hipSuccess &&
-              hipHostMalloc(&c->h_k, sizeof(double) * (m + 1), hipHostMallocDefault) == hipSuccess;
+              hipHostMalloc(&c->h_k, sizeof(double) * (2 * m + 3), hipHostMallocDefault) == hipSuccess;
     if (!ok) return fail(c, NMG_ENOMEM, "Krylov vectors");
     c->km = m;
     return NMG_OK;
@@ -787,6 +787,25 @@ int kdots(nmg_ctx *c, long n, const double *V, int nv, const double *w, double *
     HIPCHK(c, hipMemcpyAsync(c->h_k, c->kdots, sizeof(double) * nv, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (int k = 0; k < nv; ++k) out[k] = c->h_k[k];
+    return NMG_OK;
+}
+
+// Two passes of Gram-Schmidt of w against V_0 .. V_{nv-1}: the coefficients of
+// each in h and h2, then the 2-norm of w.  The coefficients stay on the device
+// between the passes; one transfer brings all of them (synchronizes).
+int korthogonalize(nmg_ctx *c, long n, const double *V, int nv, double *w, double *h, double *h2,
+                   double *nrm)
+{
+    double *d = c->kdots;
+    HIPCHK(c, launch_multidot(n, V, n, nv, w, c->kpart, d, c->stream));
+    HIPCHK(c, launch_axpy_dot(n, V, n, nv, d, false, w, c->kpart, d + nv, c->stream));
+    HIPCHK(c, launch_axpy_dot(n, V, n, nv, d + nv, true, w, c->kpart, d + 2 * nv, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->h_k, d, sizeof(double) * (2 * nv + 1), hipMemcpyDeviceToHost,
+                             c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    for (int k = 0; k < nv; ++k) h[k] = c->h_k[k];
+    for (int k = 0; k < nv; ++k) h2[k] = c->h_k[nv + k];
+    *nrm = std::sqrt(c->h_k[2 * nv]);
     return NMG_OK;
 }
 
@@ -846,14 +865,9 @@ int adjoint_gmres(nmg_ctx *c, int m, double tol, int max_cycles, int *cycles)
             ++k;
             HIPCHK(c, launch_apply(c->dim, L0.G, (const double *)L0.A, (const double *)L0.x, w,
                                    c->stream));
-            if ((rc = kdots(c, n, V, j + 1, w, h.data()))) return rc;
-            if ((rc = kaxpy(c, n, V, j + 1, h.data(), 1.0, w))) return rc;
-            if ((rc = kdots(c, n, V, j + 1, w, h2.data()))) return rc;
-            if ((rc = kaxpy(c, n, V, j + 1, h2.data(), 1.0, w))) return rc;
-            for (int i = 0; i <= j; ++i) Hij(i, j) = h[i] + h2[i];
             double nrm = 0.0;
-            if ((rc = kdots(c, n, w, 1, w, &nrm))) return rc;
-            nrm = std::sqrt(nrm);
+            if ((rc = korthogonalize(c, n, V, j + 1, w, h.data(), h2.data(), &nrm))) return rc;
+            for (int i = 0; i <= j; ++i) Hij(i, j) = h[i] + h2[i];
             Hij(j + 1, j) = nrm;
             for (int i = 0; i < j; ++i) {
                 const double a = Hij(i, j), bb = Hij(i + 1, j);

@@ -292,6 +292,10 @@ hipError_t launch_lin_res_vec(int dim, const LevelGeom &G, const double *A, cons
                               const double *x, double *r, hipStream_t s);
 hipError_t launch_multidot(long n, const double *V, long ld, int nv, const double *w,
                            double *partial, double *out, hipStream_t s);
+// w -= sum_k c[k] V_k (c on the device), then out[k] = <V_k, w>, k < nv, or with
+// self out[0] = <w, w>.
+hipError_t launch_axpy_dot(long n, const double *V, long ld, int nv, const double *c, bool self,
+                           double *w, double *partial, double *out, hipStream_t s);
 hipError_t launch_multi_axpy(long n, const double *V, long ld, int nv, const double *c, double a,
                              double *w, hipStream_t s);
 

@@ -69,9 +69,11 @@ def measured_traffic():
 # operations: Step 2.1 BLU-SGS, assembly, Galerkin levels, n_mg cycles of
 # Algorithm 0 with the same-colour elision and zero starts, the update.
 
-def newton_step_bytes(p, nx, ny, coarse_cells=1024, pair_cells=1 << 17):
+def newton_step_bytes(p, nx, ny, coarse_cells=1024, run=5):
     """Algorithmic HBM bytes of one Newton step of a 2D solve with parameters
-    p on an nx x ny grid (per-unit byte counts in the comments)."""
+    p on an nx x ny grid (per-unit byte counts in the comments), with the
+    finest level's half sweeps launched one by one as in an instrumented solve
+    and the levels between it and the coarse kernel's in runs of `run`."""
     esz = 4 if p.get("inner_fp32", 0) else 8
     NL = int(p["n_levels"])
     N = [(nx >> l) * (ny >> l) for l in range(NL + 1)]
@@ -80,9 +82,9 @@ def newton_step_bytes(p, nx, ny, coarse_cells=1024, pair_cells=1 << 17):
     full = blk + 3 * vec               # half-sweep update reading every neighbour
     zero = 9 * esz + 2 * vec           # update after a zero start (D, b, write)
     lc = next((l for l in range(NL + 1) if N[l] <= coarse_cells), NL + 1)
-    # levels whose last pre-smoothing half sweep writes its cells' residuals
-    # for the restriction (launched one half sweep per launch)
-    reuse = {l for l in range(NL) if l < lc and (l == 0 or N[l] > pair_cells)}
+    # the finest level's last pre-smoothing half sweep writes its cells'
+    # residuals for the restriction
+    reuse = {l for l in range(NL) if l < lc and l == 0}
     st = [[1, 1] for _ in range(NL + 1)]        # 1: zero, 0: stored, 2: stored + pending
     last = [-1] * (NL + 1)
     tot = [0.0]
@@ -98,7 +100,28 @@ def newton_step_bytes(p, nx, ny, coarse_cells=1024, pair_cells=1 << 17):
         st[l][c] = 0
         last[l] = c
 
+    restricted = [False]
+
+    def smooth_run(l, iters, res):
+        """Both colours' rows, b and x read and x written once per run."""
+        first = 1 if last[l] == 0 else 0
+        left = 2 * iters + 1 - first if iters > 0 else 0
+        restricted[0] = res and left > 0
+        if not left:
+            return
+        zero_start = st[l][first ^ 1] in (1, 3)
+        pending = max(st[l]) >= 2
+        last[l] = first ^ ((left - 1) & 1)
+        runs = (left + run - 1) // run
+        tot[0] += N[l] * runs * (blk + 3 * vec)
+        tot[0] += N[l] * ((vec / 4 if pending else 0) - (vec if zero_start else 0))
+        tot[0] += N[l + 1] * vec if res else 0
+        st[l] = [0, 0]
+
     def smooth(l, iters, res_last=False):
+        restricted[0] = False
+        if 0 < l < lc:
+            return smooth_run(l, iters, res_last)
         for it in range(iters):
             for q, c in enumerate((0, 1, 1, 0)):
                 half(l, c, res_last and it == iters - 1 and q == 3)
@@ -113,12 +136,15 @@ def newton_step_bytes(p, nx, ny, coarse_cells=1024, pair_cells=1 << 17):
             last[l] = -1
 
     def cycle(l):
-        smooth(l, p["nu1"], l < NL and l in reuse)
+        smooth(l, p["nu1"], l < NL and (l in reuse or 0 < l < lc))
         if l == NL:
             smooth(l, p["nu_coarse"])
         else:
+            done = restricted[0]
             materialize(l)
-            if l in reuse:          # half the residuals stored, the other half computed
+            if done:
+                pass                # the run restricted its residual
+            elif l in reuse:        # half the residuals stored, the other half computed
                 tot[0] += N[l] / 2 * vec + N[l] / 2 * (blk + 3 * vec) + N[l + 1] * vec
             else:
                 tot[0] += N[l] * (blk + 3 * vec) + N[l + 1] * vec
@@ -155,8 +181,10 @@ def phase_ms(ctx):
 
 def timed_solves(ctx, z, U0, steps, warmup, tol, cap, label):
     """Warm-up solves, then `steps` timed solves from U0 (inputs resident in
-    HBM); returns (seconds, stats, timing of the finest full SGS sweeps, phase
-    times summed over the timed solves, the last solve's state)."""
+    HBM), then one untimed solve with the measurement hooks on, which launch the
+    finest level's half sweeps one by one between events; returns (seconds,
+    stats, timing of the finest full SGS sweeps and phase times of the
+    instrumented solve, the last timed solve's state)."""
     import torch
     for w in range(warmup):
         st = ctx.newton_mg_solve(z, U0.clone(), tol)
@@ -164,12 +192,14 @@ def timed_solves(ctx, z, U0, steps, warmup, tol, cap, label):
             label, w, st["status"], st["newton_steps"], st["init_sweeps"], st["res_l1"]),
             file=sys.stderr, flush=True)
     Us = [U0.clone() for _ in range(steps)]
-    ctx.timing_enable(True, cap)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     stats = [ctx.newton_mg_solve(z, Us[k], tol) for k in range(steps)]
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    ctx.timing_enable(True, cap)
+    ctx.newton_mg_solve(z, U0.clone(), tol)
+    torch.cuda.synchronize()
     ctx.timing_enable(False)
     for k, st in enumerate(stats):
         print("[bench] %s solve %d: %s steps=%d init=%d res=%.3e" % (
@@ -515,7 +545,7 @@ def main():
     last = stats[-1]
     n_newton = last["newton_steps"]
     ms_per_step = 1e3 * dt / args.steps
-    phases = {k: v / args.steps for k, v in ph.items()}
+    phases = ph
     roofline = sgs_roofline(tm, SGS_BYTES_2D, measured_traffic())
     roofline["kernel"] = "k_sgs_half<3, MODE_NORMAL> (finest level)"
 
@@ -548,7 +578,7 @@ def main():
             "phase_ms_per_solve": phases,
         },
         "roofline": roofline,
-        "step_roofline": step_roofline(prob, ph, args.steps, n_newton),
+        "step_roofline": step_roofline(prob, ph, 1, n_newton),
     }
     # The same solve with the FP32 inner cycle (hierarchy and smoother in
     # FP32, residual, update and stop test in FP64).
@@ -569,9 +599,9 @@ def main():
         "final_res_l1": st32[-1]["res_l1"],
         "max_abs_diff_vs_fp64": {"h": dU[0], "hu": dU[1], "hv": dU[2]},
         "max_abs_fp64": {"h": scale[0], "hu": scale[1], "hv": scale[2]},
-        "phase_ms_per_solve": {k: v / args.steps for k, v in ph32.items()},
+        "phase_ms_per_solve": ph32,
         "roofline": sgs_roofline(tm32, SGS_BYTES_2D_FP32),
-        "step_roofline": step_roofline(prob32, ph32, args.steps, st32[-1]["newton_steps"]),
+        "step_roofline": step_roofline(prob32, ph32, 1, st32[-1]["newton_steps"]),
     }
     if not args.no_extras:
         ex = {}

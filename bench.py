@@ -532,6 +532,7 @@ def main():
         dst.copy_(src)
         ctx.assemble_residual_jacobian(z, U0)
         dU = torch.zeros_like(U0)
+        ctx.timing_enable(True, 64)         # single half sweeps
         ctx.sgs(dU, 4)
         torch.cuda.synchronize()
         print("[bench] kernel probe done", file=sys.stderr, flush=True)

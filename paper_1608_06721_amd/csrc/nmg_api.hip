@@ -776,6 +776,9 @@ int kbuffers(nmg_ctx *c, int m)
               hipMalloc(&c->kcoef, sizeof(double) * (m + 1)) == hipSuccess &&
               hipHostMalloc(&c->h_k, sizeof(double) * (2 * m + 3), hipHostMallocDefault) == hipSuccess;
     if (!ok) return fail(c, NMG_ENOMEM, "Krylov vectors");
+    // The vectors run over the slots without a cell too (odd nx); the kernels
+    // that form them write cells only, and sums and updates keep a zero there.
+    HIPCHK(c, hipMemsetAsync(c->kV, 0, vb * (m + 1), c->stream));
     c->km = m;
     return NMG_OK;
 }

@@ -1129,6 +1129,17 @@ int count_pinned(nmg_ctx *c, const double *z, const double *U, int *n)
 int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params, void *stream,
                bool plan, nmg_ctx **out);
 
+// The reciprocal of the difference step for fd_quotient.  Its recipe needs
+// quotients no smaller than their differences (eps at most 1) and |e| / 2^110
+// normal; elsewhere NaN, which sends every nonzero difference to the division.
+void fd_split(Phys &P)
+{
+    bool in = P.eps <= 1.0;
+    for (int f = 0; f < 2 * P.dim; ++f) in = in && P.elen[f] >= 0x1p-900;
+    P.eps_rh = in ? 1.0 / P.eps : std::nan("");
+    P.eps_rl = std::fma(-P.eps_rh, P.eps, 1.0) / P.eps;
+}
+
 // Physics of the finest mesh for the kernels (validated arguments).
 Phys make_phys(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params)
 {
@@ -1141,8 +1152,6 @@ Phys make_phys(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params)
     P.g = params->g;
     P.alpha = params->alpha;
     P.eps = params->fd_eps;
-    P.eps_rh = 1.0 / P.eps;
-    P.eps_rl = std::fma(-P.eps_rh, P.eps, 1.0) / P.eps;
     P.h_eps = params->h_eps;
     P.eps_r = params->eps_r;
     P.tau = params->tau;
@@ -1164,6 +1173,7 @@ Phys make_phys(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params)
         P.bc[f].hash = !std::isnan(s.h);
         P.bc[f].hast = !std::isnan(s.ut);
     }
+    fd_split(P);
     return P;
 }
 

@@ -20,7 +20,7 @@ struct Phys {
     int flux, dry_pin;
     double g, alpha, eps, h_eps, eps_r, tau, pos_theta;
     double elen[4];         // |e| of W, E, S, N faces
-    double eps_rh, eps_rl;  // 1/eps as a sum: eps_rh = RN(1/eps), eps_rl the rest (fd_quotient)
+    double eps_rh, eps_rl;  // 1/eps as a sum: eps_rh = RN(1/eps), eps_rl the rest, or NaN (fd_split)
     SideDev bc[4];
 };
 

@@ -100,17 +100,17 @@ struct Row {
 
 // Solve the NC x NC block system D x = r in precision T: adjugate (cofactors
 // along row 0) times the reciprocal determinant; x = 0 when that reciprocal
-// is not finite.
+// is not finite.  Returns the determinant.
 template <class T, int NC>
-__device__ __forceinline__ void solve_block(const T *D, const T *r, T *x)
+__device__ __forceinline__ T solve_block(const T *D, const T *r, T *x)
 {
     if (NC == 2) {
         T det = D[0] * D[3] - D[1] * D[2];
         T idet = T(1) / det;
-        if (!__builtin_isfinite(idet)) { x[0] = T(0); x[1] = T(0); return; }
+        if (!__builtin_isfinite(idet)) { x[0] = T(0); x[1] = T(0); return det; }
         x[0] = (D[3] * r[0] - D[1] * r[1]) * idet;
         x[1] = (D[0] * r[1] - D[2] * r[0]) * idet;
-        return;
+        return det;
     }
     T d00 = D[0], d01 = D[1], d02 = D[2];
     T d10 = D[3], d11 = D[4], d12 = D[5];
@@ -120,10 +120,11 @@ __device__ __forceinline__ void solve_block(const T *D, const T *r, T *x)
     T C20 = d01 * d12 - d02 * d11, C21 = d02 * d10 - d00 * d12, C22 = d00 * d11 - d01 * d10;
     T det = d00 * C00 + d01 * C01 + d02 * C02;
     T idet = T(1) / det;
-    if (!__builtin_isfinite(idet)) { x[0] = T(0); x[1] = T(0); x[2] = T(0); return; }
+    if (!__builtin_isfinite(idet)) { x[0] = T(0); x[1] = T(0); x[2] = T(0); return det; }
     x[0] = (C00 * r[0] + C10 * r[1] + C20 * r[2]) * idet;
     x[1] = (C01 * r[0] + C11 * r[1] + C21 * r[2]) * idet;
     x[2] = (C02 * r[0] + C12 * r[1] + C22 * r[2]) * idet;
+    return det;
 }
 
 // Precomputed form of solve_block for blocks that many sweeps reuse: the

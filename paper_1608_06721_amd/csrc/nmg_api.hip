@@ -1742,9 +1742,13 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
     rb.add(&b->w_cells0, u, kBlock);
     {
         std::vector<long> bs(n);
-        long slots = 0;
-        for (int k = 0; k < n; ++k) slots += blu_slots(grids[k].nx, grids[k].ny, false);
-        b->blu_patch = blu_patches(b->dim, slots);
+        long slots = 0, cost[2] = {0, 0};
+        for (int k = 0; k < n; ++k) {
+            slots += blu_slots(grids[k].nx, grids[k].ny, false);
+            for (int patch = 0; patch < 2; ++patch)
+                cost[patch] += blu_cost(grids[k].nx, grids[k].ny, patch);
+        }
+        b->blu_patch = blu_patches(b->dim, slots, cost[0], cost[1]);
         for (int k = 0; k < n; ++k) bs[k] = blu_slots(grids[k].nx, grids[k].ny, b->blu_patch);
         rb.add(&b->w_blu, bs, kBlock);
     }

@@ -202,8 +202,10 @@ hipError_t launch_blu_half_io(const Phys &P, const double *z, const double *Uown
                               double *res_partial);
 int blu_half_blocks(const Phys &P, int lanes);
 // Order (patches or rows) of the one-lane kernels' slots for a launch of that
-// many cells per colour, and the slot numbers of one colour in either order.
-bool blu_patches(int dim, long slots);
+// many cells per colour, from its length (blu_cost, summed over a batch) in
+// either, and the slot numbers of one colour in either order.
+long blu_cost(int nx, int ny, bool patch);
+bool blu_patches(int dim, long slots, long cost_rows, long cost_patches);
 long blu_slots(int nx, int ny, bool patch);
 // A whole sweep in one launch (k_blu_sweep_tile) from Uin to Uout, 2D meshes
 // of at most kSweepTileMaxCells cells; with stop.ctrl as one of Step 1's.

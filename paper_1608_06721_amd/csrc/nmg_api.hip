@@ -37,6 +37,7 @@ struct Level {
     void *A = nullptr, *b = nullptr, *x = nullptr;   // double, or float (FP32 inner)
     void *xt = nullptr;     // the other buffer of x (runs of half sweeps; the two change places)
     int flip = 0;           // batches: the current x of every instance is in its xt
+    RunPlan run;            // runs of half sweeps on the level (all instances of a batch)
     int st[2] = {ST_ZERO, ST_ZERO};
     int last = -1;      // colour of the last half sweep if nothing changed since, else -1
 };
@@ -133,7 +134,6 @@ struct nmg_batch {
     WorkRange w_rchild[kMaxLevels];       // tiles of 256 children of level l's cells (restriction into l)
     WorkRange w_run[kMaxLevels][2];       // tiles of level l's runs of half sweeps without
                                           // and with a restriction
-    long run_cells[kMaxLevels] = {};      // cells of all instances
     int tile[kMaxLevels];                 // tile length of the half sweeps per level
     int persist = 0;                      // blocks of the persistent half sweep (0: one per item)
     int *d_active = nullptr, *h_active = nullptr;   // instances still iterating
@@ -308,15 +308,14 @@ int halfsweep(nmg_ctx *c, int l, int color, bool res = false)
     return NMG_OK;
 }
 
-// Cells that level l's runs of half sweeps go over, 0 where its half sweeps are
-// launched one by one (while recording, on levels of the coarse kernel and, with
-// the timing hook on, on the finest level, whose single launches it times).
-long run_cells(const nmg_ctx *c, int l)
+// Whether level l's half sweeps are launched in runs (not while recording, on
+// levels of the coarse kernel, nor, with the timing hook on, on the finest
+// level, whose single launches it times).
+bool in_runs(const nmg_ctx *c, int l)
 {
-    if (c->recording || c->dim != 2 || c->fuse < 2) return 0;
-    if (c->lc >= 0 && l >= c->lc) return 0;
-    if (l == 0 && c->timing) return 0;
-    return c->batch ? c->batch->run_cells[l] : cells(c->L[l].G);
+    if (c->recording || c->fuse < 2 || c->L[l].run.cells == 0) return false;
+    if (c->lc >= 0 && l >= c->lc) return false;
+    return l > 0 || !c->timing;
 }
 
 int sweep_mode(int st_other)
@@ -336,14 +335,14 @@ int sweep_mode(int st_other)
 // follows (c->restricted).
 int smooth_single(nmg_ctx *c, int l, int iters, bool res_last = false);
 
-int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, long ncells)
+int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last)
 {
     Level &Lv = c->L[l];
     const Level &Lc = c->L[l + 1 <= c->NL ? l + 1 : l];
     const int first = (Lv.last == 0) ? 1 : 0;
     const long total = iters > 0 ? 2L * iters + 1 - first : 0;
     const long runs = (total + c->fuse - 1) / c->fuse;
-    if (total && total / runs + (res_last && runs == 1) < run_least(ncells, c->f32))
+    if (total && total / runs + (res_last && runs == 1) < run_least(Lv.run.cells, c->f32))
         return smooth_single(c, l, iters, res_last);
     int color = first;
     for (long q = 0; q < runs; ++q) {
@@ -356,7 +355,7 @@ int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, long ncells)
             if (c->res_level == l) c->res_level = -1;
             const int mode = sweep_mode(Lv.st[color ^ 1]);
             const bool res = last && res_last;
-            const RunTile tile = run_tile(ncells, c->f32, res);
+            const RunTile tile = Lv.run.tile[res];
             if (c->batch) {
                 const nmg_batch *B = c->batch;
                 HIPCHK(c, launch_b_sgs_run(c->f32, tile, mode, res, B->d_lv + (long)l * B->n,
@@ -382,7 +381,7 @@ int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last, long ncells)
 int smooth(nmg_ctx *c, int l, int iters, bool res_last = false)
 {
     c->restricted = false;
-    if (const long n = run_cells(c, l)) return smooth_runs(c, l, iters, res_last, n);
+    if (in_runs(c, l)) return smooth_runs(c, l, iters, res_last);
     return smooth_single(c, l, iters, res_last);
 }
 
@@ -1232,6 +1231,7 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
     for (int l = 0; l <= c->NL; ++l) {
         int nx = grid->nx >> l, ny = grid->dim == 1 ? 1 : grid->ny >> l;
         c->L[l].G = make_geom(nx, ny);
+        if (c->dim == 2) c->L[l].run = run_plan(1, &c->L[l].G, c->f32);
         total += (size_t)2 * c->ne * c->L[l].G.planeP + (size_t)2 * 2 * c->nc * c->L[l].G.plane +
                  (has_xt(c) ? (size_t)2 * c->nc * c->L[l].G.plane : 0);
         total = aligned(total);
@@ -1770,11 +1770,12 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
             for (int k = 0; k < n; ++k) u[k] = cells(geom(k, l)) * (b->dim == 1 ? 2 : 4);
             rb.add(&b->w_rchild[l], u, kBlock);
         }
-        long total = 0;
-        for (int k = 0; k < n; ++k) total += cells(geom(k, l));
-        b->run_cells[l] = total;
-        for (int res = 0; res < 2 && b->dim == 2; ++res) {
-            const RunTile t = run_tile(total, b->f32, res);
+        if (b->dim == 1) continue;
+        std::vector<LevelGeom> Gs(n);
+        for (int k = 0; k < n; ++k) Gs[k] = geom(k, l);
+        t->L[l].run = run_plan(n, Gs.data(), b->f32);
+        for (int res = 0; res < 2; ++res) {
+            const RunTile t = b->inst[0]->L[l].run.tile[res];
             for (int k = 0; k < n; ++k)
                 u[k] = (long)((geom(k, l).nx + t.x - 1) / t.x) * ((geom(k, l).ny + t.y - 1) / t.y);
             rb.add(&b->w_run[l][res], u, 1);

@@ -253,12 +253,16 @@ hipError_t launch_restrict_res(int dim, bool f32, const LevelGeom &G, const void
 // `color` first, in `mode`) in one launch, 2D only, on run_tile tiles: both
 // colours are read from xin and written to xout (two buffers, except in
 // MODE_ZERO, where xin is not read); with bc the restriction of the resulting
-// residual to the next level follows.  run_tile: the tiles of such a run, with
-// or without the restriction, on a level of `cells` cells (of all instances in
-// a batch); run_least: the fewest half sweeps, a restriction counted as one,
-// that are faster as a run than one by one.
+// residual to the next level follows.  run_plan: the tiles of such runs,
+// without and with the restriction, on a level of n instances, and its cells, 0
+// if single launches are faster there; run_least: the fewest half sweeps, a
+// restriction counted as one, that are faster as a run than one by one.
 struct RunTile { int x, y; };
-RunTile run_tile(long cells, bool f32, bool res);
+struct RunPlan {
+    long cells = 0;
+    RunTile tile[2];
+};
+RunPlan run_plan(int n, const LevelGeom *G, bool f32);
 int run_least(long cells, bool f32);
 hipError_t launch_sgs_run(bool f32, RunTile tile, int mode, const LevelGeom &G, const void *A,
                           const void *b, const void *xin, void *xout, int count, int color,

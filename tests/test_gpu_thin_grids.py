@@ -79,3 +79,68 @@ def test_sweep(nx, ny):
     ctx.blu_sweep(dev(z), V)
     same(V, oracle.blu_sweep(p, U), "U after a sweep")
     ctx.close()
+
+
+def step_ms(nx, ny, **kw):
+    """Assembly and three cycles from zero."""
+    from paper_1608_06721_amd import nmg
+    p = still(nx, ny, **kw)
+    ctx = nmg.Context.from_problem(p)
+    z, U = dev(p.z), dev(p.U0)
+    x = torch.zeros_like(U)
+
+    def call():
+        ctx.assemble_residual_jacobian(z, U, want_norm=False)
+        x.zero_()
+        ctx.mg_vcycle(x, 3)
+    ms = shortest(call, 3)
+    ctx.close()
+    return ms
+
+
+@pytest.mark.parametrize("fp32", [0, 1])
+@pytest.mark.parametrize("nx,ny", [(2, 131072), (4, 65536), (6, 43692), (12, 21846), (131072, 2),
+                                   (65536, 4), (32768, 8), (8192, 2), (2, 8192)])
+def test_step_time(nx, ny, fp32, monkeypatch):
+    """No coarse levels: runs of half sweeps against half sweeps one by one."""
+    runs = step_ms(nx, ny, n_levels=0, inner_fp32=fp32)
+    monkeypatch.setenv("NMG_FUSE", "1")
+    single = step_ms(nx, ny, n_levels=0, inner_fp32=fp32)
+    print("[thin step]", nx, ny, fp32, runs, single, flush=True)
+    assert runs <= 1.5 * single
+
+
+@pytest.mark.parametrize("coarse", ["0", "1024"])
+@pytest.mark.parametrize("nx,ny,nl", [(2, 131080, 1), (8, 16384, 2), (16, 8200, 3), (34, 2048, 1),
+                                      (40000, 2, 1), (2, 4096, 1)])
+@pytest.mark.parametrize("fp32", [0, 1])
+def test_cycles(nx, ny, nl, fp32, coarse, monkeypatch):
+    from paper_1608_06721_amd import nmg
+    monkeypatch.setenv("NMG_COARSE_CELLS", coarse)
+    A, b = W.random_system(2, nx, ny, nx + ny)
+    x0 = np.random.default_rng(3).uniform(-1, 1, b.shape)
+    p = W.default_params(2, n_levels=nl, nu_coarse=3, inner_fp32=fp32)
+    prob = W.Problem("thin", 2, nx, ny, 0, 1, 0, 1, [W.wall()] * 4, p, np.zeros((ny, nx)),
+                     np.zeros_like(b))
+    print("[thin cycles]", nx, ny, nl, fp32, flush=True)
+    ctx = nmg.Context.from_problem(prob)
+    ctx.load_system(dev(A), dev(b))
+    x = dev(x0)
+    ctx.mg_vcycle(x, 2)
+    same(x, oracle.vcycles(A, b, x0, p, 2), "x after cycles")
+    ctx.close()
+
+
+def test_batch():
+    """Instances under half a tile wide beside wider ones."""
+    from paper_1608_06721_amd import nmg
+    for sizes in ([(4, 4096)] * 20, [(8, 2048), (16, 1024), (64, 64), (2048, 8)] * 5):
+        probs = [still(nx, ny, n_levels=1, max_newton=2) for nx, ny in sizes]
+        for k, p in enumerate(probs):
+            p.U0[1] += 0.01 * k
+        batch = nmg.Batch(probs)
+        Us = [dev(p.U0) for p in probs]
+        batch.newton_mg_solve([dev(p.z) for p in probs], Us, 0.0)
+        batch.close()
+        for p, U in list(zip(probs, Us))[:6]:
+            same(U, oracle.newton_solve(p, tol=0.0)[0], "U of %dx%d" % (p.nx, p.ny))

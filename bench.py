@@ -9,10 +9,10 @@ pre-smoothing, residual and FD-Jacobian assembly, Galerkin coarsening,
 red-black block-SGS multigrid cycles, relaxed update) for as many Newton steps
 as the solve needs.
 
-Prints one JSON line with the metric, the roofline of the dominant kernel
-(the finest-level block SGS half sweep, timed with hipEvents on the
-library's stream), the time per phase of Algorithm 1, a roofline of the
-whole Newton step, further workloads (the paper's default V-cycle, the FP32
+Prints one JSON line with the metric, the roofline of the finest level's
+smoothing as the solve launches it (runs of block SGS half sweeps, timed with
+hipEvents on the library's stream) and of the same half sweeps launched one by
+one, the time per phase of Algorithm 1, a roofline of the whole Newton step, further workloads (the paper's default V-cycle, the FP32
 inner cycle, the previously measured bed, the paper's 2D wet/dry example,
 batched solves, bed gradients) and the CPU oracle timed on a bounded sample.
 """
@@ -38,6 +38,9 @@ SGS_BYTES_2D_FP32 = 45 * 4 + 12 + 12 + 12
 PHASES = ["step1", "blu", "assembly", "galerkin", "norm", "cycles", "update", "final"]
 
 
+RUN = 5                     # most half sweeps in one launch
+
+
 def sgs_source_digest():
     """sha256 (first 16 hex digits) of the sources the block SGS half-sweep
     kernel is compiled from."""
@@ -48,19 +51,37 @@ def sgs_source_digest():
     return h.hexdigest()[:16]
 
 
-def measured_traffic():
-    """HBM bytes per finest-level SGS launch from the committed rocprofv3
-    counter runs, or None if the kernel's sources changed since they were taken."""
+def run_source_digest():
+    """The same of the sources of the runs of half sweeps."""
+    import hashlib
+    p = os.path.join(HERE, "paper_1608_06721_amd", "csrc", "nmg_kernels.hip")
+    return hashlib.sha256(open(p, "rb").read() + sgs_source_digest().encode()).hexdigest()[:16]
+
+
+def counter_record(digest_key, digest, value_key):
+    """A value of the committed rocprofv3 counter runs, or None if the
+    kernel's sources changed since they were taken."""
     prof = os.path.join(HERE, "profiles", "sgs_halfsweep_channel1024_f64_pmc.md")
     try:
         fields = dict(l.split(":", 1) for l in open(prof).read().splitlines()
-                      if l.startswith(("kernel_source_sha256_16:", "traffic_bytes_per_launch:")))
-        digest = sgs_source_digest()
-        if fields["kernel_source_sha256_16"].strip() != digest:
+                      if l.startswith((digest_key + ":", value_key + ":")))
+        if fields[digest_key].strip() != digest:
             return None
-        return float(fields["traffic_bytes_per_launch"])
+        return float(fields[value_key])
     except (OSError, KeyError, ValueError):
         return None
+
+
+def measured_traffic():
+    """HBM bytes per finest-level half sweep launched on its own."""
+    return counter_record("kernel_source_sha256_16", sgs_source_digest(),
+                          "traffic_bytes_per_launch")
+
+
+def measured_run_traffic():
+    """HBM bytes per finest-level run of five half sweeps."""
+    return counter_record("run_source_sha256_16", run_source_digest(),
+                          "traffic_bytes_per_run")
 
 
 # ---------------------------------------------------------------------------
@@ -71,9 +92,8 @@ def measured_traffic():
 
 def newton_step_bytes(p, nx, ny, coarse_cells=1024, run=5):
     """Algorithmic HBM bytes of one Newton step of a 2D solve with parameters
-    p on an nx x ny grid (per-unit byte counts in the comments), with the
-    finest level's half sweeps launched one by one as in an instrumented solve
-    and the levels between it and the coarse kernel's in runs of `run`."""
+    p on an nx x ny grid (per-unit byte counts in the comments), with the half
+    sweeps of the levels above the coarse kernel's in runs of `run`."""
     esz = 4 if p.get("inner_fp32", 0) else 8
     NL = int(p["n_levels"])
     N = [(nx >> l) * (ny >> l) for l in range(NL + 1)]
@@ -81,20 +101,17 @@ def newton_step_bytes(p, nx, ny, coarse_cells=1024, run=5):
     vec = 3 * esz                      # one cell's 3-vector in the hierarchy's type
     full = blk + 3 * vec               # half-sweep update reading every neighbour
     zero = 9 * esz + 2 * vec           # update after a zero start (D, b, write)
-    lc = next((l for l in range(NL + 1) if N[l] <= coarse_cells), NL + 1)
-    # the finest level's last pre-smoothing half sweep writes its cells'
-    # residuals for the restriction
-    reuse = {l for l in range(NL) if l < lc and l == 0}
+    lc = next((l for l in range(1, NL + 1) if N[l] <= coarse_cells), NL + 1)
     st = [[1, 1] for _ in range(NL + 1)]        # 1: zero, 0: stored, 2: stored + pending
     last = [-1] * (NL + 1)
     tot = [0.0]
 
-    def half(l, c, res=False):
+    def half(l, c):
         if last[l] == c:
             return
         mode_zero = st[l][c ^ 1] in (1, 3)
         n = N[l] / 2
-        tot[0] += n * (zero if mode_zero else full) + (n * vec if res and not mode_zero else 0)
+        tot[0] += n * (zero if mode_zero else full)
         if st[l][c ^ 1] >= 2:
             tot[0] += n * vec / 4           # the coarse correction read by prolongation
         st[l][c] = 0
@@ -120,11 +137,11 @@ def newton_step_bytes(p, nx, ny, coarse_cells=1024, run=5):
 
     def smooth(l, iters, res_last=False):
         restricted[0] = False
-        if 0 < l < lc:
+        if l < lc:
             return smooth_run(l, iters, res_last)
         for it in range(iters):
-            for q, c in enumerate((0, 1, 1, 0)):
-                half(l, c, res_last and it == iters - 1 and q == 3)
+            for c in (0, 1, 1, 0):
+                half(l, c)
 
     def materialize(l):
         for c in (0, 1):
@@ -136,7 +153,7 @@ def newton_step_bytes(p, nx, ny, coarse_cells=1024, run=5):
             last[l] = -1
 
     def cycle(l):
-        smooth(l, p["nu1"], l < NL and (l in reuse or 0 < l < lc))
+        smooth(l, p["nu1"], l < NL and l < lc)
         if l == NL:
             smooth(l, p["nu_coarse"])
         else:
@@ -144,8 +161,6 @@ def newton_step_bytes(p, nx, ny, coarse_cells=1024, run=5):
             materialize(l)
             if done:
                 pass                # the run restricted its residual
-            elif l in reuse:        # half the residuals stored, the other half computed
-                tot[0] += N[l] / 2 * vec + N[l] / 2 * (blk + 3 * vec) + N[l + 1] * vec
             else:
                 tot[0] += N[l] * (blk + 3 * vec) + N[l + 1] * vec
             st[l + 1] = [1, 1]
@@ -181,10 +196,10 @@ def phase_ms(ctx):
 
 def timed_solves(ctx, z, U0, steps, warmup, tol, cap, label):
     """Warm-up solves, then `steps` timed solves from U0 (inputs resident in
-    HBM), then one untimed solve with the measurement hooks on, which launch the
-    finest level's half sweeps one by one between events; returns (seconds,
-    stats, timing of the finest full SGS sweeps and phase times of the
-    instrumented solve, the last timed solve's state)."""
+    HBM), then one untimed solve with the measurement hooks on (the same launches
+    with events between them); returns (seconds, stats, timing of the finest
+    level's half sweeps and phase times of the instrumented solve, the last
+    timed solve's state)."""
     import torch
     for w in range(warmup):
         st = ctx.newton_mg_solve(z, U0.clone(), tol)
@@ -206,6 +221,50 @@ def timed_solves(ctx, z, U0, steps, warmup, tol, cap, label):
             label, k, st["status"], st["newton_steps"], st["init_sweeps"], st["res_l1"]),
             file=sys.stderr, flush=True)
     return dt, stats, ctx.timing_read(), phase_ms(ctx), Us[-1]
+
+
+def run_roofline(tm, prob, traffic=None):
+    """Of the finest level's post-smoothing runs: their own bytes (a level's
+    rows, b and x read, x written, the coarse correction added on the way)."""
+    p = prob.params
+    esz = 4 if p.get("inner_fp32", 0) else 8
+    sweeps = 2 * int(p["nu2"]) + 1              # half sweeps of a post-smoothing
+    runs = tm["launches"] / sweeps * math.ceil(sweeps / RUN)
+    n = prob.nx * prob.ny
+    per_run = n * (45 + 3 + 6 + 0.75) * esz
+    avg_ms = tm["ms"] / runs if runs else 0.0
+    achieved = per_run / (avg_ms * 1e-3) / 1e9 if runs else None
+    return dict(bound="hbm", achieved=achieved, peak=HBM_PEAK_GBS, unit="GB/s",
+                frac=(achieved / HBM_PEAK_GBS) if achieved else None,
+                traffic=(traffic / (avg_ms * 1e-3) / 1e9) if (traffic and achieved) else None,
+                traffic_bytes_per_launch=traffic, avg_launch_us=avg_ms * 1e3, launches=runs,
+                half_sweeps_per_launch=sweeps / math.ceil(sweeps / RUN),
+                us_per_half_sweep=tm["ms"] * 1e3 / max(1, tm["launches"]),
+                bytes_per_launch=per_run)
+
+
+def single_half_sweeps(nmg, prob, z, U0, reps=20, **over):
+    """Timing of finest-level half sweeps launched one by one (NMG_FUSE=1) on
+    the system assembled at the initial state."""
+    import torch
+    old = os.environ.get("NMG_FUSE")
+    os.environ["NMG_FUSE"] = "1"
+    try:
+        ctx = nmg.Context.from_problem(prob, **over)
+    finally:
+        if old is None:
+            del os.environ["NMG_FUSE"]
+        else:
+            os.environ["NMG_FUSE"] = old
+    ctx.assemble_residual_jacobian(z, U0)
+    dU = torch.zeros_like(U0)
+    ctx.sgs(dU, 4)
+    ctx.timing_enable(True, reps)
+    for _ in range(reps):
+        ctx.sgs(dU, 4)
+    tm = ctx.timing_read()
+    ctx.close()
+    return tm
 
 
 def sgs_roofline(tm, bytes_per_update, traffic=None):
@@ -523,8 +582,8 @@ def main():
     U0 = torch.from_numpy(prob.U0).cuda()
     if args.kernel_probe:
         # Counter calibration: a plain copy of a known size, then 4 block SGS
-        # iterations (red, black, red per iteration after the first) on the
-        # system assembled at the initial state.
+        # iterations (nine half sweeps) on the system assembled at the initial
+        # state.
         ctx = nmg.Context.from_problem(prob)
         src = torch.empty(64 * 1024 * 1024, dtype=torch.float64, device="cuda")
         dst = torch.empty_like(src)
@@ -532,8 +591,7 @@ def main():
         dst.copy_(src)
         ctx.assemble_residual_jacobian(z, U0)
         dU = torch.zeros_like(U0)
-        ctx.timing_enable(True, 64)         # single half sweeps
-        ctx.sgs(dU, 4)
+        ctx.sgs(dU, 4)          # NMG_FUSE=1: nine half sweeps; else two runs of them
         torch.cuda.synchronize()
         print("[bench] kernel probe done", file=sys.stderr, flush=True)
         return
@@ -547,8 +605,10 @@ def main():
     n_newton = last["newton_steps"]
     ms_per_step = 1e3 * dt / args.steps
     phases = ph
-    roofline = sgs_roofline(tm, SGS_BYTES_2D, measured_traffic())
-    roofline["kernel"] = "k_sgs_half<3, MODE_NORMAL> (finest level)"
+    roofline = run_roofline(tm, prob, measured_run_traffic())
+    roofline["kernel"] = "k_sgs_pair_run (finest level's post-smoothing, as solved)"
+    half = sgs_roofline(single_half_sweeps(nmg, prob, z, U0), SGS_BYTES_2D, measured_traffic())
+    half["kernel"] = "k_sgs_half (finest level, launched one by one; not part of the solve)"
 
     out = {
         "metric": METRIC,
@@ -579,6 +639,7 @@ def main():
             "phase_ms_per_solve": phases,
         },
         "roofline": roofline,
+        "half_sweep_roofline": half,
         "step_roofline": step_roofline(prob, ph, 1, n_newton),
     }
     # The same solve with the FP32 inner cycle (hierarchy and smoother in
@@ -601,7 +662,9 @@ def main():
         "max_abs_diff_vs_fp64": {"h": dU[0], "hu": dU[1], "hv": dU[2]},
         "max_abs_fp64": {"h": scale[0], "hu": scale[1], "hv": scale[2]},
         "phase_ms_per_solve": ph32,
-        "roofline": sgs_roofline(tm32, SGS_BYTES_2D_FP32),
+        "roofline": run_roofline(tm32, prob32),
+        "half_sweep_roofline": sgs_roofline(
+            single_half_sweeps(nmg, prob, z, U0, inner_fp32=1), SGS_BYTES_2D_FP32),
         "step_roofline": step_roofline(prob32, ph32, 1, st32[-1]["newton_steps"]),
     }
     if not args.no_extras:

@@ -227,6 +227,39 @@ int batch_flip(const nmg_ctx *c, int l)
     return c->L[l].flip | (l < c->NL ? c->L[l + 1].flip << 1 : 0);
 }
 
+// Measurement hook: an event pair around launches of half sweeps of the finest
+// level that do nothing else (no restriction, no residual output) and read
+// every block (no start from zero).  Those launched back to back within one
+// smoothing call share one pair.  timing_begin returns the pair's index or -1.
+int timing_begin(nmg_ctx *c, int l, bool want, int *pair)
+{
+    *pair = -1;
+    if (!c->timing || c->batch || l != 0 || !want) return NMG_OK;
+    const bool open = c->tgroup >= 0;
+    const int k = open ? c->tgroup : c->nrec;
+    if (k >= (int)c->ev.size()) return NMG_OK;
+    if (!open) HIPCHK(c, hipEventRecord(c->ev[k].first, c->stream));
+    *pair = k;
+    return NMG_OK;
+}
+
+// Closes pair k (-1: none) behind `count` half sweeps, the first of `color`.
+int timing_end(nmg_ctx *c, int k, int count, int color)
+{
+    if (k < 0) {
+        c->tgroup = -1;
+        return NMG_OK;
+    }
+    HIPCHK(c, hipEventRecord(c->ev[k].second, c->stream));
+    const LevelGeom &G = c->L[0].G;
+    for (int s = 0; s < count; ++s)
+        for (int j = 0; j < G.ny; ++j) c->ev_cells[k] += (G.nx - ((j + color + s) & 1) + 1) / 2;
+    c->ev_launches[k] += count;
+    if (k == c->nrec) c->nrec = k + 1;
+    c->tgroup = k;
+    return NMG_OK;
+}
+
 // res: a restriction from level l follows this half sweep; a normal-mode
 // launch then also writes the updated cells' residuals (c->rres), which the
 // restriction reads instead of recomputing them.  Any other change to the
@@ -271,14 +304,8 @@ int halfsweep(nmg_ctx *c, int l, int color, bool res = false)
         Lv.last = color;
         return NMG_OK;
     }
-    // Measurement hook: full half sweeps (all neighbour blocks read) of the
-    // finest level.  A run of them launched back to back (within one
-    // smoothing call) shares one pair of events around the whole run.
-    const bool want = c->timing && l == 0 && mode == MODE_NORMAL && !res;
-    const bool open = want && c->tgroup >= 0;
-    const int k = open ? c->tgroup : c->nrec;
-    const bool rec = want && k < (int)c->ev.size();
-    if (rec && !open) HIPCHK(c, hipEventRecord(c->ev[k].first, c->stream));
+    int pair, rc;
+    if ((rc = timing_begin(c, l, mode == MODE_NORMAL && !res, &pair))) return rc;
     if (res) {
         HIPCHK(c, launch_sgs_half_res(c->dim, c->f32, Lv.G, Lv.A, Lv.b, Lv.x, color, c->rres,
                                       stream_level(cells(Lv.G), c->nc, c->f32 ? 4 : 8),
@@ -290,32 +317,18 @@ int halfsweep(nmg_ctx *c, int l, int color, bool res = false)
                                   Lc.x, stream_level(cells(Lv.G), c->nc, c->f32 ? 4 : 8),
                                   c->stream));
     }
-    if (rec) {
-        HIPCHK(c, hipEventRecord(c->ev[k].second, c->stream));
-        long n = 0;
-        for (int j = 0; j < Lv.G.ny; ++j) n += (Lv.G.nx - ((j + color) & 1) + 1) / 2;
-        c->ev_cells[k] += n;
-        c->ev_launches[k] += 1;
-        if (!open) {
-            c->nrec = k + 1;
-            c->tgroup = k;
-        }
-    } else {
-        c->tgroup = -1;
-    }
+    if ((rc = timing_end(c, pair, 1, color))) return rc;
     Lv.st[color] = ST_VALID;
     Lv.last = color;
     return NMG_OK;
 }
 
-// Whether level l's half sweeps are launched in runs (not while recording, on
-// levels of the coarse kernel, nor, with the timing hook on, on the finest
-// level, whose single launches it times).
+// Whether level l's half sweeps are launched in runs (not while recording, nor
+// on levels of the coarse kernel).
 bool in_runs(const nmg_ctx *c, int l)
 {
     if (c->recording || c->fuse < 2 || c->L[l].run.cells == 0) return false;
-    if (c->lc >= 0 && l >= c->lc) return false;
-    return l > 0 || !c->timing;
+    return c->lc < 0 || l < c->lc;
 }
 
 int sweep_mode(int st_other)
@@ -345,6 +358,7 @@ int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last)
     if (total && total / runs + (res_last && runs == 1) < run_least(Lv.run.cells, c->f32))
         return smooth_single(c, l, iters, res_last);
     int color = first;
+    c->tgroup = -1;               // timed pairs never span other launches
     for (long q = 0; q < runs; ++q) {
         const int count = (int)(total / runs + (q < total % runs));
         const bool last = q + 1 == runs;
@@ -356,6 +370,9 @@ int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last)
             const int mode = sweep_mode(Lv.st[color ^ 1]);
             const bool res = last && res_last;
             const RunTile tile = Lv.run.tile[res];
+            int pair, rc;
+            const bool reads = mode == MODE_NORMAL || mode == MODE_PROLONG;
+            if ((rc = timing_begin(c, l, reads && !res, &pair))) return rc;
             if (c->batch) {
                 const nmg_batch *B = c->batch;
                 HIPCHK(c, launch_b_sgs_run(c->f32, tile, mode, res, B->d_lv + (long)l * B->n,
@@ -368,12 +385,14 @@ int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last)
                                          Lc.x, res ? Lc.b : nullptr, c->stream));
                 if (mode != MODE_ZERO) std::swap(Lv.x, Lv.xt);
             }
+            if ((rc = timing_end(c, pair, count, color))) return rc;
             Lv.st[0] = Lv.st[1] = ST_VALID;
             Lv.last = color ^ ((count - 1) & 1);
             c->restricted = res;
         }
         color ^= count & 1;
     }
+    c->tgroup = -1;
     return NMG_OK;
 }
 

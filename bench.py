@@ -329,7 +329,8 @@ def batched(args):
     """Batched solves of uneven independent problems: `args.batch` steady
     channels with sizes from {128, 256, 384, 512}^2, their own beds and
     inflow discharges U[0.5, 2], FP32 inner W-cycle, FP64 outer, one batch
-    solve (after an untimed one) with autotuned tiles."""
+    solve (after an untimed one).  tiles: of half sweeps launched one by one,
+    which this batch makes none of."""
     import collections
     import torch
     from paper_1608_06721_amd import nmg

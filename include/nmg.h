@@ -318,20 +318,23 @@ typedef struct nmg_batch nmg_batch;
 /* grids[n], bcs[n] (host arrays), one params for all instances, stream as in
  * nmg_create.  Allocates one hierarchy per instance plus the work lists.
  * Launch-structure switch read here (changes no bit of any result):
- * NMG_BATCH_PERSISTENT = k > 0 runs the batched half sweeps on a persistent
- * grid of k blocks per compute unit looping over the work list (default:
- * one block per work item). */
+ * NMG_BATCH_PERSISTENT = k > 0 runs the batched half sweeps that are launched
+ * one by one (all in 1D; in 2D those of NMG_FUSE=1 and of smoothings too short
+ * for runs) on a persistent grid of k blocks per compute unit looping over the
+ * work list (default: one block per work item). */
 int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs,
                      const nmg_params *params, void *stream, nmg_batch **out);
 void nmg_batch_destroy(nmg_batch *batch);
 const char *nmg_batch_last_error(const nmg_batch *batch);
 
 /* Tile-length autotuner of the batched block SGS half sweep: for every
- * level launched on its own (the coarse-kernel levels excepted), times
- * `reps` (1..1000) half sweeps with each tile length 64, 128, 256 and 512
- * cells on this batch's hierarchy and keeps the fastest.  Results do not
- * depend on the choice.  tiles_host (nullable, n_levels + 1 ints) receives
- * the chosen lengths.  Synchronizes the stream. */
+ * level whose half sweeps are launched one by one (as under
+ * NMG_BATCH_PERSISTENT; not the levels of the coarse kernel, nor those that
+ * are smoothed in runs of half sweeps, whose tiles follow from the level's
+ * size), times `reps` (1..1000) half sweeps with each tile length 64, 128, 256
+ * and 512 cells on this batch's hierarchy and keeps the fastest.  Results do
+ * not depend on the choice.  tiles_host (nullable, n_levels + 1 ints) receives
+ * the chosen lengths, 256 for the levels not tuned.  Synchronizes the stream. */
 int nmg_batch_autotune(nmg_batch *batch, int reps, int *tiles_host);
 
 /* Newton multigrid solves of every instance: z[k], U[k] are device pointers

@@ -341,22 +341,53 @@ int sweep_mode(int st_other)
     }
 }
 
-// The half sweeps of `iters` symmetric iterations on level l (colour order
-// 0, 1, 1, 0, a repeat of the last colour elided) in runs of at most c->fuse,
-// as even as they go, a run of one as a single launch, all single where runs
-// are too short.  The last run also restricts the residual where a restriction
-// follows (c->restricted).
+// The half sweeps of `iters` symmetric iterations (colour order 0, 1, 1, 0, a
+// repeat of the last colour elided, `first` the colour of the first) in runs of
+// at most c->fuse, as even as they go.  single: all launched one by one, because
+// the runs would be too short.
+struct Split {
+    long total, runs;
+    bool single;
+};
+Split split_runs(const nmg_ctx *c, int l, int iters, int first, bool res_last)
+{
+    Split s;
+    s.total = iters > 0 ? 2L * iters + 1 - first : 0;
+    s.runs = (s.total + c->fuse - 1) / c->fuse;
+    s.single = s.total && s.total / s.runs + (res_last && s.runs == 1) <
+                              run_least(c->L[l].run.cells, c->f32);
+    return s;
+}
+
+// Whether the cycles of c launch half sweeps of level l one by one (a run of one
+// is such a launch).
+bool launches_singles(const nmg_ctx *c, int l)
+{
+    const nmg_params &p = c->prm;
+    const bool coarsest = l == c->NL;
+    const struct { int iters; bool res; } calls[] = {
+        {p.nu1, !coarsest}, {coarsest ? p.nu_coarse : 0, false}, {p.nu2, false}};
+    for (const auto &q : calls)
+        for (int first = 0; first < 2 && q.iters > 0; ++first) {
+            if (!in_runs(c, l)) return true;
+            const Split s = split_runs(c, l, q.iters, first, q.res);
+            if (s.single || s.total / s.runs == 1) return true;
+        }
+    return false;
+}
+
 int smooth_single(nmg_ctx *c, int l, int iters, bool res_last = false);
 
+// A smoothing in runs (split_runs), a run of one as a single launch.  The last
+// run also restricts the residual where a restriction follows (c->restricted).
 int smooth_runs(nmg_ctx *c, int l, int iters, bool res_last)
 {
     Level &Lv = c->L[l];
     const Level &Lc = c->L[l + 1 <= c->NL ? l + 1 : l];
     const int first = (Lv.last == 0) ? 1 : 0;
-    const long total = iters > 0 ? 2L * iters + 1 - first : 0;
-    const long runs = (total + c->fuse - 1) / c->fuse;
-    if (total && total / runs + (res_last && runs == 1) < run_least(Lv.run.cells, c->f32))
-        return smooth_single(c, l, iters, res_last);
+    const Split split = split_runs(c, l, iters, first, res_last);
+    if (split.single) return smooth_single(c, l, iters, res_last);
+    const long total = split.total, runs = split.runs;
     int color = first;
     c->tgroup = -1;               // timed pairs never span other launches
     for (long q = 0; q < runs; ++q) {
@@ -1904,6 +1935,7 @@ int nmg_batch_autotune(nmg_batch *b, int reps, int *tiles_out)
     for (int l = 0; l <= b->NL && !rc; ++l) {
         b->tile[l] = kBlock;
         if (t->lc >= 0 && l >= t->lc) continue;      // runs inside the coarse-cycle kernel
+        if (!launches_singles(t, l)) continue;       // in runs, on tiles of their own
         float best = 0.0f;
         for (int ti = 0; ti < kNumTiles && !rc; ++ti) {
             const BatchLevel *lv = b->d_lv + (long)l * b->n;

@@ -17,8 +17,11 @@
  * of that neighbour's unknown.  Blocks that point out of the grid are zero.
  *
  * Ownership.  The library never frees caller memory.  It owns only the
- * workspace inside the opaque context (the multigrid hierarchy in a
- * colour-split layout, about 1.33 x 2 x (45 + 6) x 8 bytes per 2D cell).
+ * workspace inside the opaque context: the multigrid hierarchy in a
+ * colour-split layout, in 2D about 1.33 x (45 + 6) x 8 bytes per cell (half
+ * with inner_fp32), the kept iterate (24), and where they fit 1.33 x 24 for a
+ * second x of the levels smoothed in runs; a context or batch for which there is
+ * no room works without, from single launches, with the same results.
  *
  * Streams.  All work is enqueued on the HIP stream given to nmg_create and
  * is stream-ordered with the caller's work on that stream.  Entry points

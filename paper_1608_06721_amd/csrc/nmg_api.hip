@@ -61,11 +61,13 @@ struct nmg_ctx {
     int step1_graph = 1;              // Step 1 runs of kStep1Ahead sweeps replayed as graphs
     Level L[16];
     void *pool = nullptr;             // the hierarchy's allocation
+    void *runs = nullptr;             // the levels' second x buffers (alloc_spare)
     // Residuals of colour res_color of level res_level (res_level -1: none
     // valid), written by the last half sweep of a pre-smoothing for the
     // restriction that follows it: NC planes of level 0's size in the
-    // hierarchy's type (a batch's template instance points at the batch's
-    // per-instance planes instead, through its level table).
+    // hierarchy's type, if there is room (alloc_spare; a batch's template
+    // instance points at the batch's per-instance planes instead, through its
+    // level table).
     void *rres = nullptr;
     int res_level = -1, res_color = -1;
     void *At_alloc = nullptr;         // second level-0 matrix (adjoint transpose), owned
@@ -124,6 +126,7 @@ struct nmg_batch {
     BatchInst *d_inst = nullptr;
     BatchLevel *d_lv = nullptr;           // [(NL + 1) * n], level-major
     void *d_rr = nullptr;                 // each instance's residual planes (level 0's size)
+    void *d_runs = nullptr;               // each instance's second x buffers
     LevelDev *d_clv = nullptr;            // [n * kMaxLevels] coarse-kernel level tables
     WorkItem *d_work = nullptr;
     WorkRange w_cells0{nullptr, 0};       // 256-cell tiles of level 0
@@ -1243,8 +1246,46 @@ int nmg_create(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
 
 namespace {
 
-// Whether the levels have a second x buffer (runs of half sweeps).
-bool has_xt(const nmg_ctx *c) { return c->dim == 2; }
+// Device memory that the cycles are faster with and can do without: nullptr where
+// it does not fit, so that a problem that leaves no room for it still runs.
+void *alloc_spare(size_t bytes, hipStream_t s)
+{
+    void *p = nullptr;
+    if (bytes == 0) return nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (hipMemsetAsync(p, 0, bytes, s) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(p);
+        return nullptr;
+    }
+    return p;
+}
+
+// Second x buffers of c's levels that t smooths in runs, one after the other from
+// `base` (nullptr: none are handed out); returns their bytes.
+size_t place_runs(const nmg_ctx *t, nmg_ctx *c, char *base)
+{
+    size_t off = 0;
+    for (int l = 0; l <= c->NL; ++l) {
+        if (!in_runs(t, l)) continue;
+        if (base) c->L[l].xt = base + off;
+        const size_t n = (size_t)2 * c->nc * c->L[l].G.plane * (c->f32 ? 4 : 8);
+        off += (n + 255) / 256 * 256;
+    }
+    return off;
+}
+
+// Whether t's cycles launch a half sweep one by one before a restriction, which
+// then reads the residuals that the half sweep leaves (halfsweep).
+bool wants_residuals(const nmg_ctx *t)
+{
+    for (int l = 0; l < t->NL && (t->lc < 0 || l < t->lc); ++l)
+        if (launches_singles(t, l)) return true;
+    return false;
+}
 
 int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params, void *stream,
                bool plan, nmg_ctx **out)
@@ -1282,11 +1323,9 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
         int nx = grid->nx >> l, ny = grid->dim == 1 ? 1 : grid->ny >> l;
         c->L[l].G = make_geom(nx, ny);
         if (c->dim == 2) c->L[l].run = run_plan(1, &c->L[l].G, c->f32);
-        total += (size_t)2 * c->ne * c->L[l].G.planeP + (size_t)2 * 2 * c->nc * c->L[l].G.plane +
-                 (has_xt(c) ? (size_t)2 * c->nc * c->L[l].G.plane : 0);
+        total += (size_t)2 * c->ne * c->L[l].G.planeP + (size_t)2 * 2 * c->nc * c->L[l].G.plane;
         total = aligned(total);
     }
-    if (plan) total += (size_t)c->nc * c->L[0].G.plane;      // rres (not used by batches)
     char *pool = nullptr;
     if (hipMalloc(&pool, total * esz) != hipSuccess) {
         delete c;
@@ -1299,15 +1338,7 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
         Lv.A = pool + off * esz; off += (size_t)2 * c->ne * Lv.G.planeP;
         Lv.b = pool + off * esz; off += (size_t)2 * c->nc * Lv.G.plane;
         Lv.x = pool + off * esz; off += (size_t)2 * c->nc * Lv.G.plane;
-        if (has_xt(c)) {
-            Lv.xt = pool + off * esz;
-            off += (size_t)2 * c->nc * Lv.G.plane;
-        }
         off = aligned(off);
-    }
-    if (plan) {
-        c->rres = pool + off * esz;
-        off += (size_t)c->nc * c->L[0].G.plane;
     }
     long N = cells(c->L[0].G);
     int nparts = nblocks(N);
@@ -1326,6 +1357,13 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
     if (rc) {
         nmg_destroy(c);
         return rc;
+    }
+    if (plan) {         // (batches plan and allocate for all their instances)
+        c->runs = alloc_spare(place_runs(c, c, nullptr), c->stream);
+        if (c->runs) place_runs(c, c, (char *)c->runs);
+        else c->fuse = 1;
+        if (wants_residuals(c))
+            c->rres = alloc_spare((size_t)c->nc * c->L[0].G.plane * esz, c->stream);
     }
     *out = c;
     return NMG_OK;
@@ -1348,6 +1386,8 @@ void nmg_destroy(nmg_ctx *c)
         if (g) (void)hipGraphExecDestroy(g);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->pool) (void)hipFree(c->pool);
+    if (c->runs) (void)hipFree(c->runs);
+    if (c->rres) (void)hipFree(c->rres);
     if (c->At_alloc) (void)hipFree(c->At_alloc);
     for (double *q : {c->kV, c->kg, c->kx, c->kw, c->kpart, c->kdots, c->kcoef})
         if (q) (void)hipFree(q);
@@ -1831,18 +1871,40 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
             rb.add(&b->w_run[l][res], u, 1);
         }
     }
-    // residual planes of the last pre-smoothing half sweep, one per instance
-    const size_t esz = b->f32 ? sizeof(float) : sizeof(double);
-    std::vector<size_t> rr_off(n);
-    size_t rr_total = 0;
-    for (int k = 0; k < n; ++k) {
-        rr_off[k] = rr_total;
-        rr_total += (size_t)b->nc * geom(k, 0).plane * esz;
-    }
-    if (hipMalloc(&b->d_rr, rr_total) != hipSuccess) {
+    bool ok = hipMalloc(&b->d_work, sizeof(WorkItem) * rb.items.size()) == hipSuccess &&
+              hipMalloc(&b->d_lv, sizeof(BatchLevel) * (NL + 1) * n) == hipSuccess &&
+              hipMalloc(&b->d_inst, sizeof(BatchInst) * n) == hipSuccess &&
+              hipMalloc(&b->d_active, sizeof(int) * n) == hipSuccess &&
+              hipMalloc(&b->d_mask, sizeof(int) * n) == hipSuccess &&
+              hipHostMalloc(&b->h_active, sizeof(int) * n, hipHostMallocDefault) == hipSuccess &&
+              hipHostMalloc(&b->h_mask, sizeof(int) * n, hipHostMallocDefault) == hipSuccess &&
+              hipMalloc(&b->d_roff, sizeof(int) * n) == hipSuccess &&
+              hipMalloc(&b->d_rcnt, sizeof(int) * n) == hipSuccess &&
+              hipMalloc(&b->d_partial, sizeof(double) * (b->w_cells0.n + 1)) == hipSuccess &&
+              hipMalloc(&b->d_norm, sizeof(double) * n) == hipSuccess &&
+              hipHostMalloc(&b->h_norm, sizeof(double) * n, hipHostMallocDefault) == hipSuccess;
+    if (!ok) {
         nmg_batch_destroy(b);
         return NMG_ENOMEM;
     }
+    // The spare buffers come last (what the batch cannot do without has to fit):
+    // the second x buffers, and the residual planes of the last pre-smoothing half
+    // sweep, one set per instance.
+    const size_t esz = b->f32 ? sizeof(float) : sizeof(double);
+    size_t bytes = 0;
+    for (int k = 0; k < n; ++k) bytes += place_runs(t, b->inst[k], nullptr);
+    b->d_runs = alloc_spare(bytes, b->stream);
+    bytes = 0;
+    for (int k = 0; k < n && b->d_runs; ++k)
+        bytes += place_runs(t, b->inst[k], (char *)b->d_runs + bytes);
+    if (!b->d_runs) t->fuse = 1;
+    std::vector<size_t> rr_off(n);
+    bytes = 0;
+    for (int k = 0; k < n; ++k) {
+        rr_off[k] = bytes;
+        bytes += (size_t)b->nc * geom(k, 0).plane * esz;
+    }
+    if (wants_residuals(t)) b->d_rr = alloc_spare(bytes, b->stream);
     t->rres = b->d_rr;          // enables the batched residual half sweeps
     std::vector<BatchLevel> blv((size_t)(NL + 1) * n);
     for (int l = 0; l <= NL; ++l)
@@ -1857,22 +1919,6 @@ int nmg_batch_create(int n, const nmg_grid *grids, const nmg_bc *bcs, const nmg_
         nmg_ctx *c = b->inst[k];
         b->h_inst[k] = BatchInst{c->P, c->L[0].G, nullptr, nullptr, c->Ulast, c->iso,
                                  c->L[0].A, c->L[0].b, c->L[0].x, c->L[0].xt};
-    }
-    bool ok = hipMalloc(&b->d_work, sizeof(WorkItem) * rb.items.size()) == hipSuccess &&
-              hipMalloc(&b->d_lv, sizeof(BatchLevel) * blv.size()) == hipSuccess &&
-              hipMalloc(&b->d_inst, sizeof(BatchInst) * n) == hipSuccess &&
-              hipMalloc(&b->d_active, sizeof(int) * n) == hipSuccess &&
-              hipMalloc(&b->d_mask, sizeof(int) * n) == hipSuccess &&
-              hipHostMalloc(&b->h_active, sizeof(int) * n, hipHostMallocDefault) == hipSuccess &&
-              hipHostMalloc(&b->h_mask, sizeof(int) * n, hipHostMallocDefault) == hipSuccess &&
-              hipMalloc(&b->d_roff, sizeof(int) * n) == hipSuccess &&
-              hipMalloc(&b->d_rcnt, sizeof(int) * n) == hipSuccess &&
-              hipMalloc(&b->d_partial, sizeof(double) * (b->w_cells0.n + 1)) == hipSuccess &&
-              hipMalloc(&b->d_norm, sizeof(double) * n) == hipSuccess &&
-              hipHostMalloc(&b->h_norm, sizeof(double) * n, hipHostMallocDefault) == hipSuccess;
-    if (!ok) {
-        nmg_batch_destroy(b);
-        return NMG_ENOMEM;
     }
     ok = hipMemcpy(b->d_work, rb.items.data(), sizeof(WorkItem) * rb.items.size(),
                    hipMemcpyHostToDevice) == hipSuccess &&
@@ -1896,11 +1942,13 @@ void nmg_batch_destroy(nmg_batch *b)
     (void)hipStreamSynchronize(b->stream);
     for (nmg_ctx *c : b->inst) {
         c->batch = nullptr;
+        c->rres = nullptr;      // (the batch's)
         nmg_destroy(c);
     }
     if (b->d_inst) (void)hipFree(b->d_inst);
     if (b->d_lv) (void)hipFree(b->d_lv);
     if (b->d_rr) (void)hipFree(b->d_rr);
+    if (b->d_runs) (void)hipFree(b->d_runs);
     if (b->d_clv) (void)hipFree(b->d_clv);
     if (b->d_work) (void)hipFree(b->d_work);
     if (b->d_active) (void)hipFree(b->d_active);

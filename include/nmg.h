@@ -149,8 +149,10 @@ typedef struct {
  *                     one lane in its runs of half sweeps (default: four
  *                     lanes per cell in 2D where the level has at most 128
  *                     cells per colour);
- *   NMG_FUSE          most half sweeps per launch on the launched levels small
- *                     enough for runs of them: 5 (default) down to 1;
+ *   NMG_FUSE          most half sweeps per launch on the launched 2D levels: 5
+ *                     (default) down to 1; two or three on a large level, and
+ *                     those of a level two to eight cells wide, are launched
+ *                     one by one all the same;
  *   NMG_BLU_LANES     lanes per cell of every BLU-SGS half sweep (Step 1 and
  *                     Step 2.1): 1, 4 (one per evaluation of the forward
  *                     differences) or 16 (one per face and evaluation, 2D;

@@ -488,7 +488,7 @@ void set_zero(nmg_ctx *c, int l)
     if (c->res_level == l) c->res_level = -1;
 }
 
-// Algorithm 0 with gamma = 1 (V-cycle) on level l.
+// Algorithm 0 (one cycle) on level l.
 int cycle(nmg_ctx *c, int l)
 {
     const nmg_params &p = c->prm;
@@ -568,8 +568,6 @@ int build_coarse(nmg_ctx *c)
     return NMG_OK;
 }
 
-// Record the operations of the sub-cycle from level lc (which always starts
-// from a zero correction) and upload them with the level table.
 // Replace each maximal sequence of alternating half sweeps on a level in LDS
 // that has a thread per cell in the coarse-cycle kernel (fits[level]), the
 // first from stored values or from zero, by one COP_RUN: a run reads the
@@ -711,10 +709,11 @@ void coarse_level_table(const nmg_ctx *c, int l_lds, LevelDev *lv)
     }
 }
 
-// Record the two coarse programs of context c from level c->lc (with the
-// LDS plan c->l_lds) and upload the operation list.  fits: the coarsest level
-// has a thread per cell (merged runs allowed); reg_ok: level lc's half sweeps
-// may run register-resident with the exchange area at LDS byte rs_off.
+// Record the coarse program of context c from level c->lc, which always starts
+// from a zero correction (with the LDS plan c->l_lds), and upload it.  fits[l]:
+// level l has a thread per cell in the coarse-cycle kernel (merge_runs);
+// reg_ok: level lc's half sweeps may run register-resident with the exchange
+// area at LDS byte rs_off.
 int record_coarse(nmg_ctx *c, const bool *fits, bool reg_ok, long rs_off)
 {
     Level saved[16];

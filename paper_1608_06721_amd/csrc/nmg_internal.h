@@ -161,12 +161,13 @@ hipError_t launch_reduce(const double *partial, int n, double *out, hipStream_t 
 hipError_t launch_count_u8(const unsigned char *v, long n, double *partial, hipStream_t s);
 // lanes: lanes per cell, 1, 4 (k_blu_half_quad) or 16 (k_blu_half_x16, 2D;
 // 4 in 1D), or -1 to choose by the mesh: 16 in 2D on meshes of at most
-// kBluX16MaxCells cells per colour, 4 up to kBluQuadMaxCells, else 1.  Measured per half sweep, one
-// lane against four per cell: 79 against 94 us with 524,288 cells per
-// colour and 22 against 25 us with 131,072 (the arithmetic bounds these
-// launches and four lanes repeat the cell's own side and block solve), 17
-// against 10 us with 16,384 and 20-32 against 8-11 us on smaller levels
-// (there a launch lasts as long as one cell's chain of dependent arithmetic).
+// kBluX16MaxCells cells per colour, 4 up to kBluQuadMaxCells, else 1.
+// Measured per sweep (LLF, an inflow side), one, four and sixteen lanes: 145,
+// 280 and 421 us with 524,288 cells per colour, 50, 83 and 119 with 131,072, 47,
+// 50 and 65 with 65,522 (the arithmetic bounds these launches, and four lanes
+// repeat the cell's own side and block solve), 38, 30 and 39 with 32,768, 49, 30
+// and 27 with 16,562, 44, 23 and 19 with 8,192 (there a launch lasts as long as
+// one cell's chain of dependent arithmetic).
 constexpr long kBluQuadMaxCells = 1L << 16;
 // 2D meshes of at most kBluX16MaxCells cells per colour run the half sweep
 // with sixteen lanes per cell (k_blu_half_x16: one per face and evaluation).

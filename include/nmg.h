@@ -281,9 +281,9 @@ int nmg_bed_vjp(nmg_ctx *ctx, const double *z, const double *U, const double *la
  * hooks: where several half sweeps run in one launch (NMG_FUSE), it is timed
  * as a whole; launches that start from a zero correction or also restrict
  * are left out.  nmg_timing_read synchronizes the stream and returns, over the
- * recorded sequences, the summed milliseconds, the number of half sweeps (by
- * the name of old: each was a launch) and the number of cell updates they
- * performed. */
+ * recorded sequences, the summed milliseconds, the number of half sweeps
+ * (sgs_launches_host; several may have shared a launch) and the number of cell
+ * updates they performed. */
 int nmg_timing_enable(nmg_ctx *ctx, int enable, int cap);
 int nmg_timing_read(nmg_ctx *ctx, double *sgs_ms_host, int *sgs_launches_host,
                     long long *sgs_cells_host);

@@ -21,7 +21,9 @@
  * colour-split layout, in 2D about 1.33 x (45 + 6) x 8 bytes per cell (half
  * with inner_fp32), the kept iterate (24), and where they fit 1.33 x 24 for a
  * second x of the levels smoothed in runs; a context or batch for which there is
- * no room works without, from single launches, with the same results.
+ * no room works without, from single launches, with the same results, and an
+ * adjoint solve whose matrix or vectors do not fit beside it gives it back
+ * (unless cycles of the context were captured into a graph).
  *
  * Streams.  All work is enqueued on the HIP stream given to nmg_create and
  * is stream-ordered with the caller's work on that stream.  Entry points

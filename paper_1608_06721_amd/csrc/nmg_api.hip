@@ -62,6 +62,8 @@ struct nmg_ctx {
     Level L[16];
     void *pool = nullptr;             // the hierarchy's allocation
     void *runs = nullptr;             // the levels' second x buffers (alloc_spare)
+    size_t runs_bytes = 0;
+    bool captured = false;            // a graph of the caller's may hold their addresses
     // Residuals of colour res_color of level res_level (res_level -1: none
     // valid), written by the last half sweep of a pre-smoothing for the
     // restriction that follows it: NC planes of level 0's size in the
@@ -808,6 +810,48 @@ int level0_residual_norm(nmg_ctx *c, double *out)
 // or after max_cycles preconditioner applications; x is left in L[0].x
 // (materialized) and b in L[0].b.
 
+// Give back the second x buffers (the half sweeps are launched one by one from
+// now on, with the same results), for an allocation that does not fit beside
+// them; false where there are none, or a caller's graph may use them.
+bool release_runs(nmg_ctx *c)
+{
+    if (!c->runs || c->captured) return false;
+    for (int l = 0; l <= c->NL; ++l) {
+        Level &Lv = c->L[l];
+        if (!Lv.xt) continue;
+        const size_t off = (size_t)((char *)Lv.x - (char *)c->runs);
+        if ((char *)Lv.x >= (char *)c->runs && off < c->runs_bytes) {
+            const size_t n = (size_t)2 * c->nc * Lv.G.plane * (c->f32 ? 4 : 8);
+            if (hipMemcpyAsync(Lv.xt, Lv.x, n, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
+                return false;
+            std::swap(Lv.x, Lv.xt);
+        }
+        Lv.xt = nullptr;
+    }
+    c->fuse = 1;
+    (void)hipStreamSynchronize(c->stream);
+    (void)hipFree(c->runs);
+    c->runs = nullptr;
+    return true;
+}
+
+// hipMalloc, once more without the second x buffers if it does not fit.
+hipError_t alloc_beside_runs(nmg_ctx *c, void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    return release_runs(c) ? hipMalloc(p, bytes) : e;
+}
+
+// Notes whether the work enqueued now goes into a graph.
+void note_capture(nmg_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!c->captured && hipStreamIsCapturing(c->stream, &st) == hipSuccess)
+        c->captured = st != hipStreamCaptureStatusNone;
+}
+
 int kbuffers(nmg_ctx *c, int m)
 {
     if (c->km == m) return NMG_OK;
@@ -820,11 +864,13 @@ int kbuffers(nmg_ctx *c, int m)
     c->km = 0;
     const long n = 2L * c->nc * c->L[0].G.plane;
     const size_t vb = sizeof(double) * (size_t)n;
-    bool ok = hipMalloc(&c->kV, vb * (m + 1)) == hipSuccess && hipMalloc(&c->kg, vb) == hipSuccess &&
-              hipMalloc(&c->kx, vb) == hipSuccess && hipMalloc(&c->kw, vb) == hipSuccess &&
-              hipMalloc(&c->kpart, sizeof(double) * (size_t)(m + 1) * nblocks(n)) == hipSuccess &&
-              hipMalloc(&c->kdots, sizeof(double) * (2 * m + 3)) == hipSuccess &&
-              hipMalloc(&c->kcoef, sizeof(double) * (m + 1)) == hipSuccess &&
+    auto get = [&](double **p, size_t bytes) {
+        return alloc_beside_runs(c, (void **)p, bytes) == hipSuccess;
+    };
+    bool ok = get(&c->kV, vb * (m + 1)) && get(&c->kg, vb) && get(&c->kx, vb) && get(&c->kw, vb) &&
+              get(&c->kpart, sizeof(double) * (size_t)(m + 1) * nblocks(n)) &&
+              get(&c->kdots, sizeof(double) * (2 * m + 3)) &&
+              get(&c->kcoef, sizeof(double) * (m + 1)) &&
               hipHostMalloc(&c->h_k, sizeof(double) * (2 * m + 3), hipHostMallocDefault) == hipSuccess;
     if (!ok) return fail(c, NMG_ENOMEM, "Krylov vectors");
     // The vectors run over the slots without a cell too (odd nx); the kernels
@@ -1358,7 +1404,8 @@ int create_ctx(const nmg_grid *grid, const nmg_bc *bc, const nmg_params *params,
         return rc;
     }
     if (plan) {         // (batches plan and allocate for all their instances)
-        c->runs = alloc_spare(place_runs(c, c, nullptr), c->stream);
+        c->runs_bytes = place_runs(c, c, nullptr);
+        c->runs = alloc_spare(c->runs_bytes, c->stream);
         if (c->runs) place_runs(c, c, (char *)c->runs);
         else c->fuse = 1;
         if (wants_residuals(c))
@@ -1425,6 +1472,7 @@ int nmg_mg_vcycle(nmg_ctx *c, double *dU, int n_cycles)
 {
     if (!c) return NMG_EINVAL;
     if (!dU || n_cycles < 0) return fail(c, NMG_EINVAL, "null dU or negative cycle count");
+    note_capture(c);
     Level &L0 = c->L[0];
     HIPCHK(c, launch_vec_to_split(c->nc, c->f32, L0.G, dU, L0.x, c->stream));
     L0.st[0] = L0.st[1] = ST_VALID;
@@ -1444,6 +1492,7 @@ int nmg_sgs(nmg_ctx *c, int level, double *dU, int iters)
     if (!c) return NMG_EINVAL;
     if (!dU || iters < 0 || level < 0 || level > c->NL)
         return fail(c, NMG_EINVAL, "bad level, dU or iteration count");
+    note_capture(c);
     Level &Lv = c->L[level];
     HIPCHK(c, launch_vec_to_split(c->nc, c->f32, Lv.G, dU, Lv.x, c->stream));
     Lv.st[0] = Lv.st[1] = ST_VALID;
@@ -1553,7 +1602,8 @@ int nmg_adjoint_solve(nmg_ctx *c, const double *z, const double *U, const double
     Level &L0 = c->L[0];
     const size_t mbytes = (size_t)2 * c->ne * L0.G.planeP * (c->f32 ? sizeof(float) : sizeof(double));
     if (!c->At_alloc) {
-        if (hipMalloc(&c->At_alloc, mbytes) != hipSuccess) return fail(c, NMG_ENOMEM, "adjoint matrix");
+        if (alloc_beside_runs(c, &c->At_alloc, mbytes) != hipSuccess)
+            return fail(c, NMG_ENOMEM, "adjoint matrix");
         c->At_spare = c->At_alloc;
     }
     HIPCHK(c, launch_isolated(c->P, z, U, c->iso, c->stream));

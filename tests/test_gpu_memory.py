@@ -142,3 +142,51 @@ def test_no_room_for_a_batch(monkeypatch):
     print("[memory] batch left", left / MB, flush=True)
     assert left < 30 * MB
     assert all(np.array_equal(a, c) for a, c in zip(got, want))
+
+
+@pytest.mark.parametrize("krylov,captured", [(0, False), (4, False), (0, True)])
+def test_adjoint_takes_the_runs_memory(krylov, captured):
+    """The transposed matrix (1.5 GB) or the Krylov vectors (0.8 GB) fit only
+    without the second x (134 MB): given back, unless a graph may use it."""
+    from paper_1608_06721_amd import nmg
+    p = flow(N)
+    z, U = dev(p.z), dev(p.U0)
+    g = torch.ones_like(U)
+    s = torch.cuda.Stream()
+    out = {}
+    for full in (False, True):
+        with torch.cuda.stream(s):
+            ctx = nmg.Context.from_problem(p)
+            lam, x = torch.zeros_like(U), torch.zeros_like(U)
+            ctx.assemble_residual_jacobian(z, U, want_norm=False)
+            ctx.mg_vcycle(x, 1)
+            if captured:
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=s):
+                    ctx.mg_vcycle(x, 1)
+            s.synchronize()
+            keep = []
+            if full:
+                need = 8 * 45 * N * N + (8 * 3 * N * N * 8 if krylov else 0)
+                keep = fill(need - 70 * MB)
+            try:
+                ctx.adjoint_solve(z, U, g, lam, tol=0.0, max_cycles=2, krylov=krylov)
+                s.synchronize()
+                x.zero_()
+                ctx.mg_vcycle(x, 1)         # (of the adjoint's system)
+                s.synchronize()
+                out[full] = lam.cpu().numpy(), x.cpu().numpy()
+            except nmg.NMGError as e:
+                assert full and captured, e
+                s.synchronize()
+                out[full] = out[False]
+            else:
+                assert not (full and captured)
+            del keep
+            free()
+            if captured:
+                graph.replay()
+                s.synchronize()
+                del graph
+            ctx.close()
+    assert all(np.array_equal(a, b) for a, b in zip(out[False], out[True]))
